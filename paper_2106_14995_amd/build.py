@@ -12,7 +12,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIBDIR = os.path.join(PKG, "lib")
 LIB = os.path.join(LIBDIR, "libtron_mi355x.so")
 OBJDIR = os.path.join(LIBDIR, "obj")
-SOURCES = ["tron_lib.hip", "lane_br6.hip", "admm.hip", "server.hip", "design.hip", "group.hip"]
+SOURCES = ["tron_lib.hip", "lane_br6.hip", "admm.hip", "server.hip", "design.hip", "group.hip", "block.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # Packed FP32 instructions are switched off for the device code (the host pass of hipcc
 # reports that it does not know the feature; the device pass applies it: a float2

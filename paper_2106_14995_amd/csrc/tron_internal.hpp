@@ -21,7 +21,7 @@ struct LaneArgs {
     int32_t n_uniform, psize;
     int32_t lane_block;      // workgroup size of the lane kernels (64 or 256; 0 means 256)
     mt::Options opt;
-    double *ws;              // n > 128: per-instance matrix workspace in global memory
+    double *ws;              // n > 128: per-instance matrix workspace in global memory (or null)
     int64_t ws_stride;       // doubles per instance in ws (bucket slot t uses ws + t stride)
 };
 
@@ -31,6 +31,12 @@ constexpr int kLdsMaxN = 128;
 constexpr int kMaxN = 512;
 // doubles of one instance's matrix array for bucket size nmax (n rows, odd stride > n)
 __host__ __device__ inline int64_t mt_wave_matrix_doubles(int nmax) { return (int64_t)nmax * (int64_t)((nmax + 1) | 1); }
+
+// Row stride of the workspace form: an odd number of 16-double lines.
+__host__ __device__ inline int mt_block_ld(int n) { return 16 * (((n + 15) / 16) | 1); }
+// doubles of a workspace slot that holds it; a slot of mt_wave_matrix_doubles works as well, with
+// the stride (n + 1) | 1
+__host__ __device__ inline int64_t mt_block_slot_doubles(int nmax) { return (int64_t)nmax * mt_block_ld(nmax); }
 
 typedef void (*lane_launch_fn)(const LaneArgs &, hipStream_t);
 
@@ -44,6 +50,10 @@ lane_launch_fn mt_lane_launcher(tron_family fam, int N);
 // n <= nmax (nmax <= kLdsMaxN: LDS sized for nmax; larger nmax: a.ws must hold a.count
 // slots of a.ws_stride >= mt_wave_matrix_doubles(nmax) doubles).
 void mt_launch_wave(tron_family fam, const LaneArgs &a, int nmax, hipStream_t st);
+// The workgroup-per-instance kernel of the quartic family for kLdsMaxN < n <= nmax (a.ws as
+// above).
+void mt_launch_block(const LaneArgs &a, int nmax, hipStream_t st);
+void mt_prepare_block_kernels();
 // LDS bytes the wave kernel uses for one instance of size n (its bucket's footprint).
 size_t mt_wave_lds_bytes(int nmax);
 // Make the wave kernels and the BR6 lane kernel accept their largest LDS request (once per

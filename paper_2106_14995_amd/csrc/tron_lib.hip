@@ -235,8 +235,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void
     wave_body<Fam, false>(a);
 }
 
-// n > kLdsMaxN: the matrix array is the instance's slot of a global-memory workspace; the
-// LDS holds one 16 x 16 block of the factor while its panel is factored
+// The plan's wave_global: the matrix array is the instance's slot of a global-memory workspace;
+// the LDS holds one 16 x 16 block of the factor while its panel is factored
 constexpr size_t kPanelScratchBytes = sizeof(double) * 16 * 17;
 // and the substitutions park kStage steps of each lane's entries of L there (R rows each)
 template <class Fam>
@@ -293,10 +293,13 @@ static void launch_wave_fam(tron_family fam, const LaneArgs &a, int nmax, hipStr
         if (nmax <= 64) launch_wave<WaveFamHS45M<1>>(a, nmax, st);
         else launch_wave<WaveFamHS45M<2>>(a, nmax, st);
     } else {
+        // beyond LDS one wave per instance leaves most of the chip idle at the batch sizes that
+        // fit its memory, and walks its matrices through L2 alone: a workgroup per instance
+        // takes 3.5-6 times less (512 instances: n = 200 16.5 -> 4.2 ms, n = 512 151 -> 25.7 ms;
+        // three instances of n = 129 3.8 -> 1.1 ms)
         if (nmax <= 64) launch_wave<WaveFamQP4<1>>(a, nmax, st);
         else if (nmax <= kLdsMaxN) launch_wave<WaveFamQP4<2>>(a, nmax, st);
-        else if (nmax <= 256) launch_wave_global<WaveFamQP4<4>>(a, st);
-        else launch_wave_global<WaveFamQP4<8>>(a, st);
+        else mt_launch_block(a, nmax, st);
     }
 }
 
@@ -498,8 +501,26 @@ struct Bucket {
     int64_t count;     // instances in the bucket
     int32_t *d_index;  // instance list (null when the bucket is the whole batch in order)
     lane_launch_fn lane;
-    double *d_ws;      // nmax > kLdsMaxN: count slots of mt_wave_matrix_doubles(nmax) doubles
+    double *d_ws;      // nmax > kLdsMaxN: count slots of ws_stride doubles
+    int64_t ws_stride;
 };
+
+// The matrix workspace of a bucket: slots of whole lines for the block kernels (nmax > kLdsMaxN),
+// or of the plain size where those do not fit the memory left.
+static bool alloc_workspace(Bucket &b)
+{
+    b.ws_stride = mt_wave_matrix_doubles(b.nmax);
+    if (b.nmax > kLdsMaxN) {
+        const int64_t lines = std::max(b.ws_stride, mt_block_slot_doubles(b.nmax));
+        if (hipMalloc(&b.d_ws, sizeof(double) * (size_t)lines * (size_t)b.count) == hipSuccess) {
+            b.ws_stride = lines;
+            return true;
+        }
+        (void)hipGetLastError();
+        b.d_ws = nullptr;
+    }
+    return hipMalloc(&b.d_ws, sizeof(double) * (size_t)b.ws_stride * (size_t)b.count) == hipSuccess;
+}
 
 // sizes above the LDS limit go to a global-memory bucket of 256 or kMaxN
 static int global_edge(int n) { return n <= 256 ? 256 : kMaxN; }
@@ -521,6 +542,7 @@ void mt_prepare_wave_kernels()
     for (const void *k : k64) (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, small);
     for (const void *k : k128) (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, big);
     mt_prepare_br6();
+    mt_prepare_block_kernels();
 }
 
 static void launch_bucket(tron_family fam, const Bucket &b, const LaneArgs &a0, hipStream_t st)
@@ -531,7 +553,7 @@ static void launch_bucket(tron_family fam, const Bucket &b, const LaneArgs &a0, 
     }
     LaneArgs a = a0;
     a.ws = b.d_ws;
-    a.ws_stride = b.d_ws ? mt_wave_matrix_doubles(b.nmax) : 0;
+    a.ws_stride = b.ws_stride;
     launch_wave_fam(fam, a, b.nmax, st);
 }
 
@@ -790,8 +812,7 @@ static tron_err build_plan(tron_batch *h, const std::vector<int32_t> &n, hipStre
             b.nmax = h->n_uniform;
             b.lanes = 64;
             b.lane = nullptr;
-            if ((b.nmax > kLdsMaxN || (sp.wave_global && h->fam == TRON_FAMILY_QP4)) &&
-                hipMalloc(&b.d_ws, sizeof(double) * (size_t)mt_wave_matrix_doubles(b.nmax) * (size_t)b.count) != hipSuccess)
+            if ((b.nmax > kLdsMaxN || (sp.wave_global && h->fam == TRON_FAMILY_QP4)) && !alloc_workspace(b))
                 return mt_fail(TRON_ERR_NOMEM, "matrix workspace allocation failed");
         }
         h->buckets.push_back(b);
@@ -824,8 +845,7 @@ static tron_err build_plan(tron_batch *h, const std::vector<int32_t> &n, hipStre
         b.lanes = lanes;
         b.count = (int64_t)list.size();
         b.lane = fn;
-        if (lanes == 64 && (nmax > kLdsMaxN || (sp.wave_global && h->fam == TRON_FAMILY_QP4)) &&
-            hipMalloc(&b.d_ws, sizeof(double) * (size_t)mt_wave_matrix_doubles(nmax) * list.size()) != hipSuccess)
+        if (lanes == 64 && (nmax > kLdsMaxN || (sp.wave_global && h->fam == TRON_FAMILY_QP4)) && !alloc_workspace(b))
             return mt_fail(TRON_ERR_NOMEM, "matrix workspace allocation failed");
         HIP_TRY(hipMalloc(&b.d_index, sizeof(int32_t) * list.size()));
         HIP_TRY(hipMemcpyAsync(b.d_index, list.data(), sizeof(int32_t) * list.size(), hipMemcpyHostToDevice, st));

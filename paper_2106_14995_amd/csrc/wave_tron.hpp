@@ -1,8 +1,8 @@
-// wave_tron.hpp -- one trust-region Newton solve per wavefront, for 8 < n <= 512.
+// wave_tron.hpp -- one trust-region Newton solve per wavefront, for 8 < n <= 128.
 //
 // Lane l of the wave owns rows i = l + 64 r, r < R, of every vector (R = 1 up to n = 64, 2 up
-// to 128, then 4 and 8 with the matrix array in global memory). The n x n Hessian and its
-// Cholesky factor share one array (LDS up to n = 128) of n rows and odd
+// to 128). The n x n Hessian and its Cholesky factor share one array (LDS, or global memory when
+// the plan asks for it) of n rows and odd
 // row stride ld >= n + 1 (odd, so that both row and column walks touch distinct banks): the
 // Hessian's upper triangle with its diagonal, the factor's strict lower triangle below it,
 // and the factor's pivots in the spare column n. A Hessian-vector product then reads every
@@ -173,7 +173,7 @@ struct WaveFamHS45M {
         double pre[R];
         MT_UNROLL for (int r = 0; r < R; r++) pre[r] = 1.0;
         for (int j = 0; j < n; j++) {
-            const double xj = s.comp(s.x, j);
+            const double xj = s.comp(s.x.v, j);
             MT_UNROLL for (int r = 0; r < R; r++) {
                 const int i = s.row(r);
                 if (i < j) s.M[i * ld + j] = pre[r];
@@ -183,7 +183,7 @@ struct WaveFamHS45M {
         double suf[R];
         MT_UNROLL for (int r = 0; r < R; r++) suf[r] = 1.0;
         for (int j = n - 1; j >= 0; j--) {
-            const double xj = s.comp(s.x, j);
+            const double xj = s.comp(s.x.v, j);
             MT_UNROLL for (int r = 0; r < R; r++) {
                 const int i = s.row(r);
                 if (i < j) s.M[i * ld + j] = -(s.M[i * ld + j] * suf[r]);
@@ -198,13 +198,384 @@ struct WaveFamHS45M {
     }
 };
 
+// The vector-level steps of one solve on a wavefront, shared by the solvers that differ in
+// where the matrices live and who works on them (WaveTron here, BlockTron in block_tron.hpp).
+// Lane l holds rows l + 64 r, r < R, of every vector. Derived supplies the matrix steps:
+//   hmul(v, y)              y = H v
+//   fg(v, g)                f(v) and its gradient
+//   model(s, hs, v, gt, ft) hs = H s and, when it is cheaper together, f and gradient at v
+//                           (returns whether it evaluated them)
+//   hess()                  the Hessian at x
+//   precond(fm), fwd, bwd, step_norm, sync() after the start point is projected, and
+//   before_accept() when the last readers of x and g may still be on their way.
+// Vec holds the vectors that live through the whole solve: in registers (RegVec) or, where R
+// rows per lane of each would not fit, in LDS (LdsVec).
+template <int R>
+struct RegVec {
+    double v[R];
+    MT_INLINE double &operator[](int r) { return v[r]; }
+    MT_INLINE double operator[](int r) const { return v[r]; }
+};
+// the lane's rows 64 r of an array in LDS; every wave of a workgroup stores the same values
+typedef __attribute__((address_space(3))) double lds_double;
+struct LdsVec {
+    lds_double *v;
+    MT_INLINE lds_double &operator[](int r) { return v[64 * r]; }
+    MT_INLINE const lds_double &operator[](int r) const { return v[64 * r]; }
+};
+
+template <class Derived, int R_, class Vec = RegVec<R_>>
+struct TronSteps {
+    static constexpr int R = R_;
+    int n, lane;
+    Vec hd;                    // H diagonal (own rows)
+    Vec lo, hi, x, g;
+    double xs[R];
+    uint64_t lfm[R];           // free set of the last factored pass
+    bool has_l;
+    double f, delta, alphac;
+    int32_t iters;
+
+    MT_INLINE Derived &self() { return static_cast<Derived &>(*this); }
+    MT_INLINE const Derived &self() const { return static_cast<const Derived &>(*this); }
+    MT_INLINE int row(int r) const { return lane + 64 * r; }
+    MT_INLINE bool valid(int r) const { return row(r) < n; }
+
+    template <class A, class B>
+    MT_INLINE double dot(const A &a, const B &b) const
+    {
+        double s = 0.0;
+        MT_UNROLL for (int r = 0; r < R; r++) s = fma(a[r], b[r], s);
+        return uni(wave_sum(s));
+    }
+
+    // component k (< n) of a row-distributed vector, the same in every lane
+    MT_INLINE double comp(const double (&v)[R], int k) const
+    {
+        double t = v[0];
+        MT_UNROLL for (int r = 1; r < R; r++) t = (k >> 6) == r ? v[r] : t;
+        return bcast(t, k & 63);
+    }
+
+    MT_INLINE double pg_inf() const
+    {
+        double m = 0.0;
+        MT_UNROLL for (int r = 0; r < R; r++) m = fmax(m, valid(r) ? fabs(pg_comp(x[r], lo[r], hi[r], g[r])) : 0.0);
+        return uni(wave_max(m));
+    }
+
+    MT_INLINE double pg_nrm2() const
+    {
+        double s = 0.0;
+        MT_UNROLL for (int r = 0; r < R; r++) {
+            const double v = valid(r) ? pg_comp(x[r], lo[r], hi[r], g[r]) : 0.0;
+            s = fma(v, v, s);
+        }
+        return sqrt(uni(wave_sum(s)));
+    }
+
+    // bit j of a row-distributed mask; a select chain rather than a runtime index, so the
+    // mask stays in registers for every R
+    MT_INLINE bool is_free(const uint64_t (&fm)[R], int j) const
+    {
+        uint64_t w = fm[0];
+        MT_UNROLL for (int r = 1; r < R; r++) w = (j >> 6) == r ? fm[r] : w;
+        return (w >> (j & 63)) & 1ull;
+    }
+    MT_INLINE bool own_free(const uint64_t (&fm)[R], int r) const { return (fm[r] >> lane) & 1ull; }
+
+    MT_INLINE double trqsol(const double (&v)[R], const double (&p)[R]) const
+    {
+        const double ptx = dot(p, v), ptp = dot(p, p), xtx = dot(v, v);
+        const double dsq = delta * delta;
+        double disc = fma(ptx, ptx, ptp * (dsq - xtx));
+        disc = disc < 0.0 ? 0.0 : disc;
+        const double rad = sqrt(disc);
+        const double sig = ptx >= 0.0 ? (dsq - xtx) / (ptx + rad) : (rad - ptx) / ptp;
+        return sig > 0.0 ? sig : 0.0;
+    }
+
+    MT_INLINE bool cauchy_trial(double a, double (&xt)[R])
+    {
+        double st[R], hs[R];
+        MT_UNROLL for (int r = 0; r < R; r++) {
+            xt[r] = clampf(fma(-a, g[r], x[r]), lo[r], hi[r]);
+            st[r] = xt[r] - x[r];
+        }
+        if (!(dot(st, st) <= delta * delta)) return false;
+        self().hmul(st, hs);
+        double ss[R];
+        MT_UNROLL for (int r = 0; r < R; r++) ss[r] = fma(0.5, hs[r], g[r]);
+        const double gts = dot(g, st);
+        const double q = dot(st, ss);  // g's + s'Hs/2
+        return q <= kMu0 * gts;
+    }
+
+    MT_INLINE bool below_last_breakpoint(double a) const
+    {
+        bool any = false, below = false;
+        MT_UNROLL for (int r = 0; r < R; r++) {
+            const double d = -g[r];
+            const bool up = valid(r) && d > 0.0 && isfinite(hi[r]);
+            const bool dn = valid(r) && d < 0.0 && isfinite(lo[r]);
+            any = any || up || dn;
+            below = below || (up && a * d < hi[r] - x[r]) || (dn && a * d > lo[r] - x[r]);
+        }
+        const bool wany = __ballot(any) != 0ull, wbelow = __ballot(below) != 0ull;
+        return !wany || wbelow;
+    }
+
+    // From the stored step length: extrapolate by 10 while acceptable and below the largest
+    // breakpoint, keeping the last acceptable point, else interpolate by 0.1 until acceptable.
+    MT_INLINE void cauchy()
+    {
+        double a = alphac, at = a;
+        int t = 0;
+        bool up = false;  // extrapolating: xs holds an acceptable point
+        for (;;) {
+            double xt[R];
+            const bool ok = cauchy_trial(at, xt);
+            if (up && !ok) break;
+            a = at;
+            MT_UNROLL for (int r = 0; r < R; r++) xs[r] = xt[r];
+            if (ok) {
+                up = up || t == 0;
+                if (!up || t == kCauchyMax || !below_last_breakpoint(a)) break;
+                at = 10.0 * a;
+            } else {
+                if (t == kCauchyMax) break;
+                at = 0.1 * a;
+            }
+            t++;
+        }
+        alphac = a;
+    }
+
+    MT_INLINE void free_mask(const double (&v)[R], uint64_t (&fm)[R]) const
+    {
+        MT_UNROLL for (int r = 0; r < R; r++) fm[r] = __ballot(valid(r) && lo[r] < v[r] && v[r] < hi[r]);
+    }
+
+    // exact: no shift was needed, so the preconditioned matrix is the identity and the first
+    // CG step, s_hat = r_hat cut at the radius, is the whole solve (see lane_tron.hpp)
+    MT_INLINE int pcg(const uint64_t (&fm)[R], int m, const double (&rv)[R], double (&sh)[R],
+                      double cg_rtol, bool exact)
+    {
+        double rh[R], p[R];
+        MT_UNROLL for (int r = 0; r < R; r++) {
+            rh[r] = own_free(fm, r) ? -rv[r] : 0.0;
+            sh[r] = 0.0;
+        }
+        self().fwd(rh);
+        MT_UNROLL for (int r = 0; r < R; r++) p[r] = rh[r];
+        double rr = dot(rh, rh);
+        if (rr == 0.0) return kCgConv;
+        if (exact) {
+            if (rr >= delta * delta) {
+                const double sig = trqsol(sh, p);
+                MT_UNROLL for (int r = 0; r < R; r++) sh[r] = sig * p[r];
+                return kCgBnd;
+            }
+            MT_UNROLL for (int r = 0; r < R; r++) sh[r] = p[r];
+            return kCgConv;
+        }
+        const double tol2 = cg_rtol * cg_rtol * rr;
+        for (int j = 0; j < m; j++) {
+            double z[R], q[R];
+            MT_UNROLL for (int r = 0; r < R; r++) z[r] = p[r];
+            self().bwd(z);
+            self().hmul(z, q);
+            MT_UNROLL for (int r = 0; r < R; r++) q[r] = own_free(fm, r) ? q[r] : 0.0;
+            self().fwd(q);
+            const double kap_ = dot(p, q);
+            if (!(kap_ > 0.0)) {
+                const double sig = trqsol(sh, p);
+                MT_UNROLL for (int r = 0; r < R; r++) sh[r] = fma(sig, p[r], sh[r]);
+                return kCgNeg;
+            }
+            const double a = rr / kap_;
+            double tv[R];
+            MT_UNROLL for (int r = 0; r < R; r++) tv[r] = fma(a, p[r], sh[r]);
+            if (dot(tv, tv) >= delta * delta) {
+                const double sig = trqsol(sh, p);
+                MT_UNROLL for (int r = 0; r < R; r++) sh[r] = fma(sig, p[r], sh[r]);
+                return kCgBnd;
+            }
+            MT_UNROLL for (int r = 0; r < R; r++) {
+                sh[r] = tv[r];
+                rh[r] = fma(-a, q[r], rh[r]);
+            }
+            const double rrn = dot(rh, rh);
+            if (rrn <= tol2) return kCgConv;
+            const double b = rrn / rr;
+            MT_UNROLL for (int r = 0; r < R; r++) p[r] = fma(b, p[r], rh[r]);
+            rr = rrn;
+        }
+        return kCgMaxit;
+    }
+
+    MT_INLINE void subspace(double cg_rtol)
+    {
+        has_l = false;
+        for (int pass = 0; pass < n; pass++) {
+            uint64_t fm[R];
+            free_mask(xs, fm);
+            int m = 0;
+            MT_UNROLL for (int r = 0; r < R; r++) m += __builtin_popcountll(fm[r]);
+            if (m == 0) break;
+            double s[R], rv[R];
+            MT_UNROLL for (int r = 0; r < R; r++) s[r] = xs[r] - x[r];
+            self().hmul(s, rv);
+            MT_UNROLL for (int r = 0; r < R; r++) rv[r] += g[r];
+            const double shift = self().precond(fm);
+            has_l = true;
+            MT_UNROLL for (int r = 0; r < R; r++) lfm[r] = fm[r];
+            double w[R];
+            const int ex = pcg(fm, m, rv, w, cg_rtol, shift == 0.0);
+            self().bwd(w);
+            double beta = 1.0;
+            bool acc = false;
+            double xt[R];
+            for (int t = 0; t <= kSearchHalvings; t++) {
+                double d[R], hdv[R];
+                MT_UNROLL for (int r = 0; r < R; r++) {
+                    xt[r] = clampf(fma(beta, w[r], xs[r]), lo[r], hi[r]);
+                    d[r] = xt[r] - xs[r];
+                }
+                self().hmul(d, hdv);
+                double hh[R];
+                MT_UNROLL for (int r = 0; r < R; r++) hh[r] = fma(0.5, hdv[r], rv[r]);
+                const double rd = dot(rv, d);
+                const double dq = dot(d, hh);  // r'd + d'Hd/2
+                if (dq <= kMu0 * rd) { acc = true; break; }
+                beta *= 0.5;
+            }
+            if (acc) MT_UNROLL for (int r = 0; r < R; r++) xs[r] = xt[r];
+            uint64_t fm2[R];
+            free_mask(xs, fm2);
+            bool newly = false;
+            MT_UNROLL for (int r = 0; r < R; r++) newly = newly || (fm[r] & ~fm2[r]) != 0ull;
+            if (!((ex == kCgConv || ex == kCgMaxit) && newly)) break;
+        }
+    }
+
+    MT_INLINE double radius_update(double rho, double ared, double gts, double snorm, bool fin) const
+    {
+        double astar;
+        if (!fin) {
+            astar = kSig1;
+            rho = -__builtin_inf();
+        } else {
+            const double gam = -ared - gts;
+            if (gam <= 0.0) astar = kSig3;
+            else {
+                astar = -0.5 * gts / gam;
+                if (astar < kSig1) astar = kSig1;
+            }
+        }
+        if (rho <= kEta0) return dmin((astar > kSig1 ? astar : kSig1) * snorm, kSig2 * delta);
+        if (rho <= kEta1) return dmax(kSig1 * delta, dmin(astar * snorm, kSig2 * delta));
+        if (rho < kEta2) return dmax(kSig1 * delta, dmin(astar * snorm, kSig3 * delta));
+        return dmax(delta, dmin(astar * snorm, kSig3 * delta));
+    }
+
+    MT_INLINE int32_t solve(const Options &o, double delta_in, double alphac_in)
+    {
+        iters = 0;
+        delta = 0.0;
+        alphac = 1.0;
+        f = __builtin_nan("");
+        bool bad = false;
+        MT_UNROLL for (int r = 0; r < R; r++) bad = bad || (valid(r) && !(lo[r] <= hi[r]));
+        if (__ballot(bad) != 0ull) return kBadBounds;
+        MT_UNROLL for (int r = 0; r < R; r++) x[r] = clampb(x[r], lo[r], hi[r]);
+        self().sync();
+        {
+            double x1[R], g1[R];
+            MT_UNROLL for (int r = 0; r < R; r++) x1[r] = x[r];
+            f = self().fg(x1, g1);
+            MT_UNROLL for (int r = 0; r < R; r++) g[r] = g1[r];
+        }
+        bool fin = true;
+        MT_UNROLL for (int r = 0; r < R; r++) fin = fin && isfinite(g[r]);
+        fin = isfinite(f) && __ballot(!fin) == 0ull;
+        if (!fin) return kNonfinite;
+        if (pg_inf() <= o.gtol) return kConverged;
+        if (o.warm && delta_in > 0.0) delta = delta_in;
+        else if (o.delta0 > 0.0) delta = o.delta0;
+        else {
+            delta = pg_nrm2();
+            if (delta == 0.0) delta = 1.0;
+        }
+        if (o.warm && alphac_in > 0.0) alphac = alphac_in;
+        self().hess();
+        int32_t status;
+        for (;;) {
+            cauchy();
+            subspace(o.cg_rtol);
+            double s[R], hs[R];
+            MT_UNROLL for (int r = 0; r < R; r++) s[r] = xs[r] - x[r];
+            const double snorm = self().step_norm(s);
+            double gt[R], ft = 0.0;
+            const bool have_ft = self().model(s, hs, xs, gt, ft);
+            double hh[R];
+            MT_UNROLL for (int r = 0; r < R; r++) hh[r] = fma(0.5, hs[r], g[r]);
+            const double gts = dot(g, s);
+            const double pred = -dot(s, hh);
+            iters++;
+            if (!(pred > 0.0)) { status = kStalled; break; }
+            if (!have_ft) ft = self().fg(xs, gt);
+            const bool tfin = isfinite(ft);
+            double ared = f - ft;
+            if (tfin && pred <= kAredSwitch * (fabs(f) > 1.0 ? fabs(f) : 1.0)) {
+                double sg[R];
+                MT_UNROLL for (int r = 0; r < R; r++) sg[r] = g[r] + gt[r];
+                ared = -0.5 * dot(sg, s);
+            }
+            const double rho = tfin ? ared / pred : -__builtin_inf();
+            delta = radius_update(rho, ared, gts, snorm, tfin);
+            const bool accept = rho > kEta0;
+            if (accept) {
+                self().before_accept();
+                MT_UNROLL for (int r = 0; r < R; r++) { x[r] = xs[r]; g[r] = gt[r]; }
+                f = ft;
+            }
+            bool ok = true;
+            MT_UNROLL for (int r = 0; r < R; r++) ok = ok && isfinite(g[r]);
+            ok = isfinite(f) && __ballot(!ok) == 0ull;
+            if (!ok) { status = kNonfinite; break; }
+            if (pg_inf() <= o.gtol) { status = kConverged; break; }
+            if (iters >= o.max_iter) { status = kMaxIter; break; }
+            const double tiny = kStallRel * (fabs(f) > 1.0 ? fabs(f) : 1.0);
+            if (tfin && fabs(ared) <= tiny && pred <= tiny) { status = kStalled; break; }
+            if (accept) self().hess();
+        }
+        return status;
+    }
+};
+
 // One trust-region Newton solve per wave for the family Fam, Fam::R rows per lane
 // (n <= 64 R).
-// kGlobal: the matrix array M lives in global memory (a device workspace, for n > 128)
-// instead of LDS; only the scope of the ordering between the lanes' writes and reads changes.
+// kGlobal: the matrix array M lives in global memory (a device workspace, when the plan asks for
+// it) instead of LDS; only the scope of the ordering between the lanes' writes and reads changes.
 template <class Fam, bool kGlobal = false>
-struct WaveTron {
+struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
     static constexpr int R = Fam::R;
+    using Steps = TronSteps<WaveTron<Fam, kGlobal>, Fam::R>;
+    using Steps::n;
+    using Steps::lane;
+    using Steps::hd;
+    using Steps::lo;
+    using Steps::hi;
+    using Steps::x;
+    using Steps::lfm;
+    using Steps::has_l;
+    using Steps::row;
+    using Steps::valid;
+    using Steps::dot;
+    using Steps::comp;
+    using Steps::is_free;
+    using Steps::own_free;
 
     // order LDS writes before other lanes' LDS reads (the wave's LDS operations run in order)
     MT_INLINE void lds_sync() const
@@ -228,29 +599,14 @@ struct WaveTron {
         }
     }
     Fam fam;
-    int n, ld, lane;
+    int ld;
     double *M;                 // LDS: H upper with diagonal, L strict lower, pivots in column n
     double *P;                 // with M in global memory: LDS copy of a panel's 16 x 16 block
                                // of L (row stride 17), so that its columns meet at wave scope
     double *Q;                 // with M in global memory: kStage steps of each lane's entries of
                                // L, parked in LDS by the substitutions (slot (t R + r) 64 + lane)
-    static constexpr int kStage = R >= 8 ? 4 : 8;  // 32 values in flight per lane
-    double hd[R];              // H diagonal (own rows)
-    double lo[R], hi[R], x[R], g[R], xs[R], dinv[R];
-    uint64_t lfm[R];           // free set of the last factored pass
-    bool has_l;
-    double f, delta, alphac;
-    int32_t iters;
-
-    MT_INLINE int row(int r) const { return lane + 64 * r; }
-    MT_INLINE bool valid(int r) const { return row(r) < n; }
-
-    MT_INLINE double dot(const double (&a)[R], const double (&b)[R]) const
-    {
-        double s = 0.0;
-        MT_UNROLL for (int r = 0; r < R; r++) s = fma(a[r], b[r], s);
-        return uni(wave_sum(s));
-    }
+    static constexpr int kStage = 8;
+    double dinv[R];
 
     // H_kj (upper triangle, diagonal included) sits at min(j,k) ld + max(j,k) = min(j,k)
     // (ld - 1) + j + k: with blk = M + k + j0 for a block of columns j = j0 + u (u a
@@ -342,14 +698,6 @@ struct WaveTron {
             y[r] = valid(r) ? (acc[r][0] + acc[r][1]) + (acc[r][2] + acc[r][3]) : 0.0;
     }
 
-    // component k (< n) of a row-distributed vector, the same in every lane
-    MT_INLINE double comp(const double (&v)[R], int k) const
-    {
-        double t = v[0];
-        MT_UNROLL for (int r = 1; r < R; r++) t = (k >> 6) == r ? v[r] : t;
-        return bcast(t, k & 63);
-    }
-
     MT_INLINE void load(const double *__restrict__ p, const double *__restrict__ lop,
                         const double *__restrict__ hip_, const double *__restrict__ x0p)
     {
@@ -368,32 +716,13 @@ struct WaveTron {
 
     MT_INLINE void hess() { fam.hess(*this); }
 
-    MT_INLINE double pg_inf() const
-    {
-        double m = 0.0;
-        MT_UNROLL for (int r = 0; r < R; r++) m = fmax(m, valid(r) ? fabs(pg_comp(x[r], lo[r], hi[r], g[r])) : 0.0);
-        return uni(wave_max(m));
-    }
+    MT_INLINE void before_accept() const {}
 
-    MT_INLINE double pg_nrm2() const
+    MT_INLINE bool model(const double (&s)[R], double (&hs)[R], const double (&)[R], double (&)[R], double &) const
     {
-        double s = 0.0;
-        MT_UNROLL for (int r = 0; r < R; r++) {
-            const double v = valid(r) ? pg_comp(x[r], lo[r], hi[r], g[r]) : 0.0;
-            s = fma(v, v, s);
-        }
-        return sqrt(uni(wave_sum(s)));
+        hmul(s, hs);
+        return false;
     }
-
-    // bit j of a row-distributed mask; a select chain rather than a runtime index, so the
-    // mask stays in registers for every R
-    MT_INLINE bool is_free(const uint64_t (&fm)[R], int j) const
-    {
-        uint64_t w = fm[0];
-        MT_UNROLL for (int r = 1; r < R; r++) w = (j >> 6) == r ? fm[r] : w;
-        return (w >> (j & 63)) & 1ull;
-    }
-    MT_INLINE bool own_free(const uint64_t (&fm)[R], int r) const { return (fm[r] >> lane) & 1ull; }
 
     // Cholesky factor of H_FF + alpha I with the identity outside F: the factor's strict lower
     // triangle into M's lower part, its pivots into column n, their reciprocals into dinv.
@@ -493,7 +822,7 @@ struct WaveTron {
         return !bad;
     }
 
-    // The same panel step with M in global memory (4 or 8 rows per lane), in two passes that
+    // The same panel step with M in global memory, in two passes that
     // keep 16 values per lane live instead of 16 per row slot. First the register slot that
     // holds the panel's rows, pipelined as above, with the panel's 16 x 16 block of L and its
     // pivot reciprocals mirrored in LDS (P, row stride 17, reciprocal in column 16) so that
@@ -768,178 +1097,6 @@ struct WaveTron {
         MT_UNROLL for (int r = 0; r < R; r++) b[r] = valid(r) ? b[r] * dinv[r] : b[r];
     }
 
-    MT_INLINE double trqsol(const double (&v)[R], const double (&p)[R]) const
-    {
-        const double ptx = dot(p, v), ptp = dot(p, p), xtx = dot(v, v);
-        const double dsq = delta * delta;
-        double disc = fma(ptx, ptx, ptp * (dsq - xtx));
-        disc = disc < 0.0 ? 0.0 : disc;
-        const double rad = sqrt(disc);
-        const double sig = ptx >= 0.0 ? (dsq - xtx) / (ptx + rad) : (rad - ptx) / ptp;
-        return sig > 0.0 ? sig : 0.0;
-    }
-
-    MT_INLINE bool cauchy_trial(double a, double (&xt)[R])
-    {
-        double st[R], hs[R];
-        MT_UNROLL for (int r = 0; r < R; r++) {
-            xt[r] = clampf(fma(-a, g[r], x[r]), lo[r], hi[r]);
-            st[r] = xt[r] - x[r];
-        }
-        if (!(dot(st, st) <= delta * delta)) return false;
-        hmul(st, hs);
-        double ss[R];
-        MT_UNROLL for (int r = 0; r < R; r++) ss[r] = fma(0.5, hs[r], g[r]);
-        const double gts = dot(g, st);
-        const double q = dot(st, ss);  // g's + s'Hs/2
-        return q <= kMu0 * gts;
-    }
-
-    MT_INLINE bool below_last_breakpoint(double a) const
-    {
-        bool any = false, below = false;
-        MT_UNROLL for (int r = 0; r < R; r++) {
-            const double d = -g[r];
-            const bool up = valid(r) && d > 0.0 && isfinite(hi[r]);
-            const bool dn = valid(r) && d < 0.0 && isfinite(lo[r]);
-            any = any || up || dn;
-            below = below || (up && a * d < hi[r] - x[r]) || (dn && a * d > lo[r] - x[r]);
-        }
-        const bool wany = __ballot(any) != 0ull, wbelow = __ballot(below) != 0ull;
-        return !wany || wbelow;
-    }
-
-    MT_INLINE void cauchy()
-    {
-        double a = alphac;
-        double xt[R];
-        if (cauchy_trial(a, xt)) {
-            MT_UNROLL for (int r = 0; r < R; r++) xs[r] = xt[r];
-            for (int t = 0; t < kCauchyMax; t++) {
-                if (!below_last_breakpoint(a)) break;
-                const double a2 = 10.0 * a;
-                if (!cauchy_trial(a2, xt)) break;
-                a = a2;
-                MT_UNROLL for (int r = 0; r < R; r++) xs[r] = xt[r];
-            }
-        } else {
-            for (int t = 0; t < kCauchyMax; t++) {
-                a = 0.1 * a;
-                if (cauchy_trial(a, xt)) break;
-            }
-            MT_UNROLL for (int r = 0; r < R; r++) xs[r] = xt[r];
-        }
-        alphac = a;
-    }
-
-    MT_INLINE void free_mask(const double (&v)[R], uint64_t (&fm)[R]) const
-    {
-        MT_UNROLL for (int r = 0; r < R; r++) fm[r] = __ballot(valid(r) && lo[r] < v[r] && v[r] < hi[r]);
-    }
-
-    // exact: no shift was needed, so the preconditioned matrix is the identity and the first
-    // CG step, s_hat = r_hat cut at the radius, is the whole solve (see lane_tron.hpp)
-    MT_INLINE int pcg(const uint64_t (&fm)[R], int m, const double (&rv)[R], double (&sh)[R],
-                      double cg_rtol, bool exact)
-    {
-        double rh[R], p[R];
-        MT_UNROLL for (int r = 0; r < R; r++) {
-            rh[r] = own_free(fm, r) ? -rv[r] : 0.0;
-            sh[r] = 0.0;
-        }
-        fwd(rh);
-        MT_UNROLL for (int r = 0; r < R; r++) p[r] = rh[r];
-        double rr = dot(rh, rh);
-        if (rr == 0.0) return kCgConv;
-        if (exact) {
-            if (rr >= delta * delta) {
-                const double sig = trqsol(sh, p);
-                MT_UNROLL for (int r = 0; r < R; r++) sh[r] = sig * p[r];
-                return kCgBnd;
-            }
-            MT_UNROLL for (int r = 0; r < R; r++) sh[r] = p[r];
-            return kCgConv;
-        }
-        const double tol2 = cg_rtol * cg_rtol * rr;
-        for (int j = 0; j < m; j++) {
-            double z[R], q[R];
-            MT_UNROLL for (int r = 0; r < R; r++) z[r] = p[r];
-            bwd(z);
-            hmul(z, q);
-            MT_UNROLL for (int r = 0; r < R; r++) q[r] = own_free(fm, r) ? q[r] : 0.0;
-            fwd(q);
-            const double kap_ = dot(p, q);
-            if (!(kap_ > 0.0)) {
-                const double sig = trqsol(sh, p);
-                MT_UNROLL for (int r = 0; r < R; r++) sh[r] = fma(sig, p[r], sh[r]);
-                return kCgNeg;
-            }
-            const double a = rr / kap_;
-            double tv[R];
-            MT_UNROLL for (int r = 0; r < R; r++) tv[r] = fma(a, p[r], sh[r]);
-            if (dot(tv, tv) >= delta * delta) {
-                const double sig = trqsol(sh, p);
-                MT_UNROLL for (int r = 0; r < R; r++) sh[r] = fma(sig, p[r], sh[r]);
-                return kCgBnd;
-            }
-            MT_UNROLL for (int r = 0; r < R; r++) {
-                sh[r] = tv[r];
-                rh[r] = fma(-a, q[r], rh[r]);
-            }
-            const double rrn = dot(rh, rh);
-            if (rrn <= tol2) return kCgConv;
-            const double b = rrn / rr;
-            MT_UNROLL for (int r = 0; r < R; r++) p[r] = fma(b, p[r], rh[r]);
-            rr = rrn;
-        }
-        return kCgMaxit;
-    }
-
-    MT_INLINE void subspace(double cg_rtol)
-    {
-        has_l = false;
-        for (int pass = 0; pass < n; pass++) {
-            uint64_t fm[R];
-            free_mask(xs, fm);
-            int m = 0;
-            MT_UNROLL for (int r = 0; r < R; r++) m += __builtin_popcountll(fm[r]);
-            if (m == 0) break;
-            double s[R], rv[R];
-            MT_UNROLL for (int r = 0; r < R; r++) s[r] = xs[r] - x[r];
-            hmul(s, rv);
-            MT_UNROLL for (int r = 0; r < R; r++) rv[r] += g[r];
-            const double shift = precond(fm);
-            has_l = true;
-            MT_UNROLL for (int r = 0; r < R; r++) lfm[r] = fm[r];
-            double w[R];
-            const int ex = pcg(fm, m, rv, w, cg_rtol, shift == 0.0);
-            bwd(w);
-            double beta = 1.0;
-            bool acc = false;
-            double xt[R];
-            for (int t = 0; t <= kSearchHalvings; t++) {
-                double d[R], hdv[R];
-                MT_UNROLL for (int r = 0; r < R; r++) {
-                    xt[r] = clampf(fma(beta, w[r], xs[r]), lo[r], hi[r]);
-                    d[r] = xt[r] - xs[r];
-                }
-                hmul(d, hdv);
-                double hh[R];
-                MT_UNROLL for (int r = 0; r < R; r++) hh[r] = fma(0.5, hdv[r], rv[r]);
-                const double rd = dot(rv, d);
-                const double dq = dot(d, hh);  // r'd + d'Hd/2
-                if (dq <= kMu0 * rd) { acc = true; break; }
-                beta *= 0.5;
-            }
-            if (acc) MT_UNROLL for (int r = 0; r < R; r++) xs[r] = xt[r];
-            uint64_t fm2[R];
-            free_mask(xs, fm2);
-            bool newly = false;
-            MT_UNROLL for (int r = 0; r < R; r++) newly = newly || (fm[r] & ~fm2[r]) != 0ull;
-            if (!((ex == kCgConv || ex == kCgMaxit) && newly)) break;
-        }
-    }
-
     MT_INLINE double step_norm(const double (&s)[R]) const
     {
         if (!has_l) return sqrt(dot(s, s));
@@ -979,93 +1136,6 @@ struct WaveTron {
         return sqrt(dot(t, t));
     }
 
-    MT_INLINE double radius_update(double rho, double ared, double gts, double snorm, bool fin) const
-    {
-        double astar;
-        if (!fin) {
-            astar = kSig1;
-            rho = -__builtin_inf();
-        } else {
-            const double gam = -ared - gts;
-            if (gam <= 0.0) astar = kSig3;
-            else {
-                astar = -0.5 * gts / gam;
-                if (astar < kSig1) astar = kSig1;
-            }
-        }
-        if (rho <= kEta0) return dmin((astar > kSig1 ? astar : kSig1) * snorm, kSig2 * delta);
-        if (rho <= kEta1) return dmax(kSig1 * delta, dmin(astar * snorm, kSig2 * delta));
-        if (rho < kEta2) return dmax(kSig1 * delta, dmin(astar * snorm, kSig3 * delta));
-        return dmax(delta, dmin(astar * snorm, kSig3 * delta));
-    }
-
-    MT_INLINE int32_t solve(const Options &o, double delta_in, double alphac_in)
-    {
-        iters = 0;
-        delta = 0.0;
-        alphac = 1.0;
-        f = __builtin_nan("");
-        bool bad = false;
-        MT_UNROLL for (int r = 0; r < R; r++) bad = bad || (valid(r) && !(lo[r] <= hi[r]));
-        if (__ballot(bad) != 0ull) return kBadBounds;
-        MT_UNROLL for (int r = 0; r < R; r++) x[r] = clampb(x[r], lo[r], hi[r]);
-        sync();
-        f = fg(x, g);
-        bool fin = true;
-        MT_UNROLL for (int r = 0; r < R; r++) fin = fin && isfinite(g[r]);
-        fin = isfinite(f) && __ballot(!fin) == 0ull;
-        if (!fin) return kNonfinite;
-        if (pg_inf() <= o.gtol) return kConverged;
-        if (o.warm && delta_in > 0.0) delta = delta_in;
-        else if (o.delta0 > 0.0) delta = o.delta0;
-        else {
-            delta = pg_nrm2();
-            if (delta == 0.0) delta = 1.0;
-        }
-        if (o.warm && alphac_in > 0.0) alphac = alphac_in;
-        hess();
-        int32_t status;
-        for (;;) {
-            cauchy();
-            subspace(o.cg_rtol);
-            double s[R], hs[R];
-            MT_UNROLL for (int r = 0; r < R; r++) s[r] = xs[r] - x[r];
-            const double snorm = step_norm(s);
-            hmul(s, hs);
-            double hh[R];
-            MT_UNROLL for (int r = 0; r < R; r++) hh[r] = fma(0.5, hs[r], g[r]);
-            const double gts = dot(g, s);
-            const double pred = -dot(s, hh);
-            iters++;
-            if (!(pred > 0.0)) { status = kStalled; break; }
-            double gt[R];
-            const double ft = fg(xs, gt);
-            const bool tfin = isfinite(ft);
-            double ared = f - ft;
-            if (tfin && pred <= kAredSwitch * (fabs(f) > 1.0 ? fabs(f) : 1.0)) {
-                double sg[R];
-                MT_UNROLL for (int r = 0; r < R; r++) sg[r] = g[r] + gt[r];
-                ared = -0.5 * dot(sg, s);
-            }
-            const double rho = tfin ? ared / pred : -__builtin_inf();
-            delta = radius_update(rho, ared, gts, snorm, tfin);
-            const bool accept = rho > kEta0;
-            if (accept) {
-                MT_UNROLL for (int r = 0; r < R; r++) { x[r] = xs[r]; g[r] = gt[r]; }
-                f = ft;
-            }
-            bool ok = true;
-            MT_UNROLL for (int r = 0; r < R; r++) ok = ok && isfinite(g[r]);
-            ok = isfinite(f) && __ballot(!ok) == 0ull;
-            if (!ok) { status = kNonfinite; break; }
-            if (pg_inf() <= o.gtol) { status = kConverged; break; }
-            if (iters >= o.max_iter) { status = kMaxIter; break; }
-            const double tiny = kStallRel * (fabs(f) > 1.0 ? fabs(f) : 1.0);
-            if (tfin && fabs(ared) <= tiny && pred <= tiny) { status = kStalled; break; }
-            if (accept) hess();
-        }
-        return status;
-    }
 };
 
 }  // namespace mt

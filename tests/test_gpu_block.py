@@ -1,0 +1,74 @@
+"""GPU parity of the workgroup-per-instance kernels (quartic family) against the CPU oracle, at
+the sizes where their tiles, panels and blocks of rows end: multiples of 16 and 64 and their
+neighbours. The bars are those of tests/parity.py.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2106_14995_amd import workloads as W
+from parity import check_parity, oracle_ref
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tron():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2106_14995_amd import tron as T
+    T.lib()
+    return T
+
+
+def result(r):
+    import torch
+    torch.cuda.synchronize()
+    return {k: v.cpu().numpy() for k, v in zip(("x", "f", "status", "iters"), r)}
+
+
+def batch(count, n):
+    """count instances; the first has a third of its variables fixed, and the second starts
+    outside its box."""
+    bt = W.qp4_batch(count, n, config_id=300 + n)
+    bt.hi[:n:3] = bt.lo[:n:3]
+    bt.x0[n:2 * n] = 3.0
+    return bt
+
+
+@pytest.mark.parametrize("n", [129, 143, 144, 145, 160, 161, 191, 192, 193, 255, 256, 257, 273, 320, 383, 449, 511, 512])
+def test_edges(tron, n):
+    bt = batch(3, n)
+    h = tron.Batch(bt.family, n, batch=bt.batch)
+    check_parity(bt, result(h.solve(*tron.to_device(bt))), oracle_ref(bt), convex=True)
+    h.close()
+
+
+@pytest.mark.parametrize("n", [130, 200, 321])
+def test_workspace_strides_agree(tron, n):
+    """A handle's workspace slots hold rows of whole lines, the allocation-free call's do not:
+    the same bits either way, alone and among others."""
+    bt = batch(4, n)
+    d = tron.to_device(bt)
+    h = tron.Batch(bt.family, n, batch=4)
+    a, b = result(h.solve(*d)), result(tron.solve_noalloc(bt.family, n, 4, *d))
+    h.close()
+    one = bt.subset([2])
+    h = tron.Batch(bt.family, n, batch=1)
+    c = result(h.solve(*tron.to_device(one)))
+    h.close()
+    for k in a:
+        assert np.array_equal(a[k], b[k]), k
+        m = n if k == "x" else 1
+        assert np.array_equal(a[k][2 * m:3 * m], c[k]), k
+
+
+@pytest.mark.parametrize("n", [144, 193, 257, 400])
+def test_shift_retries(tron, n):
+    """Half-rank Q: the first factorisations meet non-positive pivots and are repeated."""
+    bt = W.qp4_half_rank_batch(3, n, config_id=95)
+    st = oracle.solve(bt)["stats"]
+    assert np.all(st[:, 3] > st[:, 6]), "no shifted retry in the oracle"
+    h = tron.Batch(bt.family, n, batch=3)
+    check_parity(bt, result(h.solve(*tron.to_device(bt))), oracle_ref(bt), convex=True)
+    h.close()
