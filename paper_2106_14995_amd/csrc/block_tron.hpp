@@ -42,83 +42,6 @@ MT_INLINE uint64_t uni64(uint64_t v)
 MT_INLINE lds_double *uni_p(lds_double *q) { return (lds_double *)(uintptr_t)(uint32_t)uni_i((int)(uint32_t)(uintptr_t)q); }
 MT_INLINE glb_double *uni_p(glb_double *q) { return (glb_double *)uni64((uint64_t)q); }
 
-// Row broadcasts read lanes that must be switched on: none of these stands in a condition that
-// differs between lanes. A source written just before takes two wait states.
-
-// value of lane S of each 16-lane row in every lane of the row
-template <int S>
-MT_INLINE double row_bcast(double v)
-{
-    double d;
-    asm("s_nop 1\n\t"
-        "v_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf"
-        : "=v"(d) : "v"(v), "n"(S));
-    return d;
-}
-// d -= (value of q in lane S of the lane's 16-lane row) * m, in one instruction. The broadcast
-// rides on the multiply-add (its source register may have been written just before, which
-// takes two wait states), so a row of a panel's update costs one instruction, not three.
-template <int S>
-MT_INLINE void fnma_row(double &d, double q, double m)
-{
-    asm("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, %1, -%2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
-        : "+&v"(d) : "v"(q), "v"(m), "n"(S));
-}
-// d0..d3 -= (q in lanes S, S + 1, S + 2, S + 3) * m
-template <int S>
-MT_INLINE void fnma_row4(double &d0, double &d1, double &d2, double &d3, double q, double m)
-{
-    asm("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, %4, -%5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %1, %4, -%5 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %2, %4, -%5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %3, %4, -%5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
-        : "+&v"(d0), "+&v"(d1), "+&v"(d2), "+&v"(d3)
-        : "v"(q), "v"(m), "n"(S), "n"(S + 1), "n"(S + 2), "n"(S + 3));
-}
-// d += (q in lane S) m0 + (q in lane S + 1) m1 + ..., one after the other
-template <int S>
-MT_INLINE void fma_row4(double &d, double q, double m0, double m1, double m2, double m3)
-{
-    asm("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %0, %1, %3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %0, %1, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %0, %1, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
-        : "+&v"(d)
-        : "v"(q), "v"(m0), "v"(m1), "v"(m2), "v"(m3), "n"(S), "n"(S + 1), "n"(S + 2), "n"(S + 3));
-}
-// d -= (q in lane S) m0, then lane S + D, S + 2 D, S + 3 D
-template <int S, int D>
-MT_INLINE void fnma_row4x(double &d, double q, double m0, double m1, double m2, double m3)
-{
-    asm("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, %1, -%2 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %0, %1, -%3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %0, %1, -%4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %0, %1, -%5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
-        : "+&v"(d)
-        : "v"(q), "v"(m0), "v"(m1), "v"(m2), "v"(m3), "n"(S), "n"(S + D), "n"(S + 2 * D), "n"(S + 3 * D));
-}
-template <int S>
-MT_INLINE void fma_row(double &d, double q, double m)
-{
-    asm("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
-        : "+&v"(d) : "v"(q), "v"(m), "n"(S));
-}
-// d -= (q0 in lane S) m0, then (q1 in lane S) m1: a column pair of a triangular solve, its even
-// column into e and its odd one into o
-template <int S>
-MT_INLINE void fnma_pair(double &e, double &o, double q0, double m0, double q1, double m1)
-{
-    asm("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, %2, -%3 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-        "v_fmac_f64_dpp %1, %4, -%5 row_newbcast:%6 row_mask:0xf bank_mask:0xf"
-        : "+&v"(e), "+&v"(o) : "v"(q0), "v"(m0), "v"(q1), "v"(m1), "n"(S));
-}
-
 template <int R_, int W_, bool kGlobal>
 struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
     static constexpr int R = R_, W = W_, kRows = 64 * R;
@@ -139,9 +62,8 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
     typedef typename MatrixPtr<kGlobal>::type MPtr;
 
     // LDS, in doubles from the start of the workgroup's dynamic allocation
-    static constexpr int kHalf = 2 * 4 * kRows;                   // four accumulators, two products
-    static constexpr int oA = 0;                                  // partial sums
-    static constexpr int oD = oA + (kGlobal ? 1 : 2) * kHalf;     // reciprocal pivots
+    static constexpr int oA = 0;                                  // partial sums: four, two products
+    static constexpr int oD = oA + 2 * 4 * kRows;                 // reciprocal pivots
     static constexpr int oPV = oD + kRows;                        // pivots
     static constexpr int oY = oPV + kRows;                        // substitution results
     static constexpr int oHD = oY + kRows;                        // H's diagonal
@@ -177,7 +99,6 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
     }
 
     Ctx k;
-    int par;      // LDS form: which half of the partial-sum buffers is next
     LdsVec qd, c;
     double kap;
 
@@ -205,7 +126,6 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
         k.p = (glb_double *)pp;
         k.n = n;
         k.lane = lane;
-        par = 0;
         hd.v = k.L0 + oHD + lane;
         qd.v = k.L0 + oQD + lane;
         lo.v = k.L0 + oVec + lane;
@@ -292,16 +212,15 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
     }
 
     template <int NV>
-    static MT_INLINE void product_body(const Ctx &ka, int o0, int o1, int par)
+    static MT_INLINE void product_body(const Ctx &ka, int o0, int o1)
     {
         const Ctx k = ka.scalar();
         const int n = k.n, lane = k.lane;
         lds_double *V = k.L0 + oV;
         if constexpr (!kGlobal) {
-            // wave: one slot of rows, one of the four accumulators. Partial sums go to
-            // alternating buffers: their readers need no barrier of their own.
+            // wave: one slot of rows, one of the four accumulators
             static_assert(W == 4 * R, "one wave per row slot and accumulator");
-            lds_double *A = k.L0 + oA + uni_i(par) * kHalf;
+            lds_double *A = k.L0 + oA;
             const int sl = k.w % R, u = k.w / R;
             const int i = lane + 64 * sl, ii = i < n ? i : 0;
             double d[NV], a[NV];
@@ -407,22 +326,14 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
         }
         __syncthreads();
     }
-    static MT_STEP void product1(Ctx k, int o0, int par) { product_body<1>(k, o0, o0, par); }
-    static MT_STEP void product2(Ctx k, int o0, int o1, int par) { product_body<2>(k, o0, o1, par); }
-
-    // the partial sums of the product or lt_product just made
-    MT_INLINE int turn()
-    {
-        const int o = oA + (kGlobal ? 0 : par * kHalf);
-        par ^= 1;
-        return o;
-    }
+    static MT_STEP void product1(Ctx k, int o0) { product_body<1>(k, o0, o0); }
+    static MT_STEP void product2(Ctx k, int o0, int o1) { product_body<2>(k, o0, o1); }
 
     MT_INLINE void hmul(const double (&v)[R], double (&y)[R])
     {
         operand(0, v);
-        product1(k, oHD, par);
-        sums(turn(), y);
+        product1(k, oHD);
+        sums(oA, y);
     }
 
     MT_INLINE double f_of(const double (&v)[R], const double (&y)[R], double (&gr)[R]) const
@@ -441,8 +352,8 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
     {
         double y[R];
         operand(0, v);
-        product1(k, oQD, par);
-        sums(turn(), y);
+        product1(k, oQD);
+        sums(oA, y);
         return f_of(v, y, gr);
     }
 
@@ -452,10 +363,9 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
         double y[R];
         operand(0, s);
         operand(1, v);
-        product2(k, oHD, oQD, par);
-        const int o = turn();
-        sums(o, hs);
-        sums(o + 4 * kRows, y);
+        product2(k, oHD, oQD);
+        sums(oA, hs);
+        sums(oA + 4 * kRows, y);
         ft = f_of(v, y, gt);
         return true;
     }
@@ -614,13 +524,13 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
 
     // Column C of the diagonal block (lane il of each 16-lane row holds row il): its entry of
     // the pivot row, the pivot, the scale, then its products off the columns after it, the sum
-    // over even columns in sv and over odd ones in s1; the newest column comes last. Each row's
-    // reciprocal pivot goes straight to the block's column 16.
+    // over even columns in sv and over odd ones in s1; the newest column comes last. Rows and
+    // columns outside F need no masks: S is the identity there, so their entries stay 0 and
+    // their pivots 1. The reciprocal pivot goes straight to the block's column 16.
     template <int C>
-    static MT_INLINE void diag_column(double (&sv)[16], double (&s1)[16], uint32_t fw, bool ownf, bool &bad, lds_double *P)
+    static MT_INLINE void diag_column(double (&sv)[16], double (&s1)[16], int cols, bool &bad, lds_double *P)
     {
         if constexpr (C < 16) {
-            const bool fj = (fw >> C) & 1u;
             double s = sv[C] + s1[C], own = s;
             if constexpr (C > 0) own = fma(-sv[C - 1], sv[C - 1], s);  // in lane C, the pivot's own update
             const double d = row_bcast<C>(own);
@@ -629,10 +539,10 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
                 fnma_row<C>(s, sv[C - 1], sv[C - 1]);
                 diag_tail<C - 1, C + 1>(sv, s1);
             }
-            bad = bad || (fj && !(d > 0.0));
-            P[C * 17 + 16] = fj ? rinv : 1.0;
-            sv[C] = (fj && ownf) ? s * rinv : 0.0;
-            diag_column<C + 1>(sv, s1, fw, ownf, bad, P);
+            bad = bad || (C < cols && !(d > 0.0));
+            P[C * 17 + 16] = rinv;
+            sv[C] = s * rinv;
+            diag_column<C + 1>(sv, s1, cols, bad, P);
         }
     }
     template <int C, int C2>
@@ -649,17 +559,9 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
         }
     }
 
-    // bits of the 16 columns from j0 that are in F and below n
-    static MT_INLINE uint32_t panel_bits(const Ctx &k, int j0)
-    {
-        const uint32_t b = (uint32_t)(word(k, j0 >> 6) >> (j0 & 63)) & 0xFFFFu;
-        return j0 + 16 <= k.n ? b : b & ((1u << (k.n - j0)) - 1u);
-    }
-
     static MT_INLINE void diag_block(const Ctx &k, int j0)
     {
         const int il = k.lane & 15, i = j0 + il, n = k.n;
-        const uint32_t fw = panel_bits(k, j0);
         lds_double *P = k.L0 + oP;
         double sv[16], s1[16];
         // Entries right of the diagonal and rows past n hold whatever was there: they only meet
@@ -671,14 +573,14 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
             sv[cc] = !kGlobal && cc == il ? own : v;
             s1[cc] = 0.0;
         }
-        const bool ownf = (fw >> il) & 1u;
+        const bool ownf = (word(k, j0 >> 6) >> (i & 63)) & 1ull;
         bool bad = false;
-        diag_column<0>(sv, s1, fw, ownf, bad, P);
+        diag_column<0>(sv, s1, n - j0, bad, P);
         if (k.lane < 16) {
             MT_UNROLL for (int cc = 0; cc < 16; cc++) P[il * 17 + cc] = sv[cc];
             wave_order();
             if (i < n) {
-                k.L0[oD + i] = P[il * 17 + 16];
+                k.L0[oD + i] = ownf ? P[il * 17 + 16] : 1.0;
                 k.L0[oPV + i] = ownf ? P[il * 17 + il] : 1.0;  // d / sqrt(d)
             }
             if (il == 0) k.L0[oF] = bad ? 1.0 : 0.0;
@@ -690,30 +592,17 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
     // cc of the block broadcast from lane cc's q). kLate: the newest column goes with its even or
     // odd fellows (rows past the panel's own 64 in the workspace form); otherwise it comes last.
     template <bool kLate, int C>
-    static MT_INLINE void row_column(double (&t)[16], const double (&q)[16], double qr, uint32_t fw, bool fi)
+    static MT_INLINE void row_column(double (&t)[16], const double (&q)[16], double qr)
     {
         if constexpr (C < 16) {
             double p0 = t[C], p1 = 0.0;
             row_sums<C, 0, kLate ? C : C - 1>(t, q, p0, p1);
             double v = p0 + p1;
             if constexpr (!kLate && C > 0) fnma_row<C>(v, q[C - 1], t[C - 1]);
-            const bool on = fi && ((fw >> C) & 1u);
-            const double r = v * row_bcast<C>(qr);  // (outside the selection: every lane takes part)
-            t[C] = on ? r : 0.0;
-            row_column<kLate, C + 1>(t, q, qr, fw, fi);
+            t[C] = v * row_bcast<C>(qr);
+            row_column<kLate, C + 1>(t, q, qr);
         }
     }
-    template <int C, int C1, int E>
-    static MT_INLINE void row_sums(const double (&t)[16], const double (&q)[16], double &p0, double &p1)
-    {
-        if constexpr (C1 + 1 < E) {
-            fnma_pair<C>(p0, p1, q[C1], t[C1], q[C1 + 1], t[C1 + 1]);
-            row_sums<C, C1 + 2, E>(t, q, p0, p1);
-        } else if constexpr (C1 < E) {
-            fnma_row<C>(p0, q[C1], t[C1]);  // C1 is even
-        }
-    }
-
     // wave w: the rows of block (j0 / 64) + w that are below the panel
     static MT_INLINE void rows_below(const Ctx &k, int j0)
     {
@@ -731,10 +620,8 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
         }
         const int sl = (j0 >> 6) + k.w;
         if (64 * sl >= n || 64 * sl + 63 < j0 + 16) return;
-        const uint32_t fw = panel_bits(k, j0);
         const int i = 64 * sl + lane;
         const bool in = i >= j0 + 16 && i < n;
-        const bool fi = in && ((word(k, sl) >> lane) & 1ull);
         double t[16], q[16];
         lds_double *src;
         if constexpr (kGlobal) src = S + (in ? i - j0 : 16) * 17;
@@ -744,8 +631,8 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
             q[cc] = P[(lane & 15) * 17 + cc];
         }
         const double qr = P[(lane & 15) * 17 + 16];
-        if (kGlobal && k.w > 0) row_column<true, 0>(t, q, qr, fw, fi);
-        else row_column<false, 0>(t, q, qr, fw, fi);
+        if (kGlobal && k.w > 0) row_column<true, 0>(t, q, qr);
+        else row_column<false, 0>(t, q, qr);
         if (in) MT_UNROLL for (int cc = 0; cc < 16; cc++) src[cc] = t[cc];
         if constexpr (kGlobal) {
             if (in) MT_UNROLL for (int cc = 0; cc < 16; cc++) k.M[(j0 + cc) * ld + i] = t[cc];
@@ -864,25 +751,6 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
     // its results go to LDS, and after one barrier every row still to come subtracts their 16
     // columns. The entries for the next 16 columns are loaded meanwhile.
     // ---------------------------------------------------------------------------------
-    template <int T, bool kUp>
-    static MT_INLINE void block_solve(double &b, double dv, const double (&dl)[16])
-    {
-        if constexpr (T < 16) {
-            constexpr int S = kUp ? 15 - T : T;
-            fnma_row<S>(b, b * dv, dl[S]);
-            block_solve<T + 1, kUp>(b, dv, dl);
-        }
-    }
-    template <bool kUp>
-    static MT_INLINE void block_update(double &b, double y, const double (&l)[16])
-    {
-        constexpr int D = kUp ? -1 : 1, F = kUp ? 15 : 0;
-        fnma_row4x<F, D>(b, y, l[F], l[F + D], l[F + 2 * D], l[F + 3 * D]);
-        fnma_row4x<F + 4 * D, D>(b, y, l[F + 4 * D], l[F + 5 * D], l[F + 6 * D], l[F + 7 * D]);
-        fnma_row4x<F + 8 * D, D>(b, y, l[F + 8 * D], l[F + 9 * D], l[F + 10 * D], l[F + 11 * D]);
-        fnma_row4x<F + 12 * D, D>(b, y, l[F + 12 * D], l[F + 13 * D], l[F + 14 * D], l[F + 15 * D]);
-    }
-
     // kUp false: L y = b; true: L^T y = b, blocks and rows in descending order. bb: this wave's
     // rows of b; the results are left in LDS.
     template <bool kUp>
@@ -931,7 +799,7 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
             if (k.w == blk >> 2) {
                 // every 16-lane row runs the steps; only the block's own row keeps them
                 double t = bb;
-                block_solve<0, kUp>(t, dv, dl);
+                block_solve<kUp>(t, dv, dl, n - 16 * blk);
                 const bool own = (lane >> 4) == (blk & 3);
                 bb = own ? t : bb;
                 const double y = bb * dv;
@@ -977,13 +845,13 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
 
     // L^T s in four partial sums by k mod 4 (see wave_tron.hpp); W / R waves share the sums of
     // one slot of rows
-    static MT_STEP void lt_product(Ctx ka, int par)
+    static MT_STEP void lt_product(Ctx ka)
     {
         constexpr int kGroups = W / R, kOwn = 4 / kGroups;
         static_assert(kGroups * R == W && kOwn * kGroups == 4, "waves per row slot");
         const Ctx k = ka.scalar();
         const int n = k.n, ld = k.ld;
-        lds_double *A = k.L0 + oA + (kGlobal ? 0 : uni_i(par) * kHalf);
+        lds_double *A = k.L0 + oA;
         const int sl = k.w % R, ug = k.w / R;
         const int i = k.lane + 64 * sl;
         double acc[kOwn];
@@ -1035,9 +903,9 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
     {
         if (!has_l) return sqrt(dot(s, s));
         operand(0, s);
-        lt_product(k, par);
+        lt_product(k);
         double y[R], t[R];
-        sums(turn(), y);
+        sums(oA, y);
         MT_UNROLL for (int r = 0; r < R; r++) t[r] = valid(r) ? fma(k.L0[oPV + row(r)], s[r], y[r]) : 0.0;
         return sqrt(dot(t, t));
     }

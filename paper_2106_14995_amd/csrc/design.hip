@@ -109,7 +109,8 @@ __global__ __launch_bounds__(64) void chol_kernel(int variant, int64_t count, in
     int rc;
     if (variant == TRON_CHOL_BLOCKED_MFMA) {
         // the solver's layout: the matrix's upper triangle with its diagonal at row stride
-        // (n + 1) | 1, the factor's strict lower triangle below it, its pivots in column n
+        // (n + 1) | 1, the factor's strict lower triangle below it, its pivots before their
+        // square roots in column n
         mt::WaveTron<mt::WaveFamQP4<1>, false> s;
         s.n = n;
         s.ld = (n + 1) | 1;
@@ -125,7 +126,8 @@ __global__ __launch_bounds__(64) void chol_kernel(int variant, int64_t count, in
         wave_sync();
         for (int e = threadIdx.x; e < n * n; e += 64) {
             const int r = e / n, c = e - r * n;
-            Lp[e] = c < r ? sm[r * s.ld + c] : (c == r ? sm[r * s.ld + n] : 0.0);
+            const double d = sm[r * s.ld + n];
+            Lp[e] = c < r ? sm[r * s.ld + c] : (c == r ? d * mt::rsqrt_pos(d) : 0.0);
         }
         // the first pivot that is not positive: every pivot before it was
         const int i = threadIdx.x;

@@ -211,23 +211,10 @@ __device__ __forceinline__ void wave_body(const LaneArgs &a)
     wave_solve<Fam, kGlobal>(a, b, kGlobal ? a.ws + t * a.ws_stride : smem, smem);
 }
 
-// Two builds of the same solver. Buckets of small n fit many instances per CU, so their
-// kernel is held to three waves per SIMD's worth of registers. From n_max = kWaveBigN on,
-// the LDS request already limits residency to about two waves per SIMD, so that build gets
-// the registers it asks for.
-constexpr int kWaveBigN = 48;
-
+// Two builds of the same solver: one held to three waves per SIMD's worth of registers (it
+// spills a few), one that gets what it asks for (two waves per SIMD).
 template <class Fam>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void wave_kernel(LaneArgs a) { wave_body<Fam, false>(a); }
-
-// n_max <= kWaveTinyN: the LDS request (8.4 KB at 32) allows four or more instances per SIMD,
-// so this variant is held to four waves' worth of registers
-constexpr int kWaveTinyN = 32;
-template <class Fam>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void wave_kernel_tiny(LaneArgs a)
-{
-    wave_body<Fam, false>(a);
-}
 
 template <class Fam>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void wave_kernel_big(LaneArgs a)
@@ -251,6 +238,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void
     wave_body<Fam, true>(a);
 }
 
+// From n_max = kWaveBigN on the LDS request already limits residency to about two waves per SIMD,
+// and a batch of up to two waves per SIMD of the chip has no use for a third.
+constexpr int kWaveBigN = 48;
+constexpr int64_t kWaveFewCount = 2048;
+
 static size_t wave_lds_bytes(int nmax) { return sizeof(double) * (size_t)nmax * (size_t)((nmax + 1) | 1); }
 
 template <class Fam>
@@ -263,12 +255,10 @@ static void launch_wave(const LaneArgs &a, int nmax, hipStream_t st)
     if constexpr (Fam::R > 1) {
         hipLaunchKernelGGL((wave_kernel_big<Fam>), dim3((unsigned)a.count), dim3(64), lds, st, a);
     } else {
-        if (nmax >= kWaveBigN)
+        if (nmax >= kWaveBigN || a.count <= kWaveFewCount)
             hipLaunchKernelGGL((wave_kernel_big<Fam>), dim3((unsigned)a.count), dim3(64), lds, st, a);
-        else if (nmax > kWaveTinyN)
-            hipLaunchKernelGGL((wave_kernel<Fam>), dim3((unsigned)a.count), dim3(64), lds, st, a);
         else
-            hipLaunchKernelGGL((wave_kernel_tiny<Fam>), dim3((unsigned)a.count), dim3(64), lds, st, a);
+            hipLaunchKernelGGL((wave_kernel<Fam>), dim3((unsigned)a.count), dim3(64), lds, st, a);
     }
 }
 
@@ -536,8 +526,7 @@ void mt_prepare_wave_kernels()
     using namespace mt;
     const int big = (int)wave_lds_bytes(128), small = (int)wave_lds_bytes(64);
     const void *k64[] = {(const void *)wave_kernel<WaveFamQP4<1>>, (const void *)wave_kernel_big<WaveFamQP4<1>>,
-                         (const void *)wave_kernel<WaveFamHS45M<1>>, (const void *)wave_kernel_big<WaveFamHS45M<1>>,
-                         (const void *)wave_kernel_tiny<WaveFamQP4<1>>, (const void *)wave_kernel_tiny<WaveFamHS45M<1>>};
+                         (const void *)wave_kernel<WaveFamHS45M<1>>, (const void *)wave_kernel_big<WaveFamHS45M<1>>};
     const void *k128[] = {(const void *)wave_kernel_big<WaveFamQP4<2>>, (const void *)wave_kernel_big<WaveFamHS45M<2>>};
     for (const void *k : k64) (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, small);
     for (const void *k : k128) (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, big);

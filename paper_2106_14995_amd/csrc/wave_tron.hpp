@@ -10,10 +10,16 @@
 // special case on the diagonal.
 // Every decision of the method is taken on wave-reduced, wave-uniform values (the free set
 // is a 64-bit ballot), so the 64 lanes never diverge.
-// Sums use a butterfly of lane swaps (every lane ends with the same bits); the pivots and
-// solution components of the triangular solves are broadcast with readlane. The Cholesky
-// factorisation is blocked in panels of 16 columns: FP64 matrix-core products form each
-// panel from the columns before it, and the panel is factored in registers (chol_panels).
+// Sums use a butterfly of lane swaps (every lane ends with the same bits). What one row passes to
+// the others (an operand of a product, a row of a panel, a substitution's results) rides on the
+// multiply-add that uses it, as a row broadcast: sixteen values lie in the sixteen lanes of every
+// 16-lane row, and a multiply-add takes one of them for its whole row. That is one instruction
+// where a pair of readlanes and the multiply-add were three, and its chain is shorter. The
+// Cholesky factorisation is blocked in panels of 16 columns: FP64 matrix-core products form each
+// panel from the columns before it, and the panel is factored in registers (chol_lds); the
+// substitutions run in blocks of 16 rows. Per batch, against the form that broadcast by readlane
+// and solved row by row: 2,048 x n = 64 0.86 -> 0.60 ms, 4,096 x n = 48 0.67 -> 0.47 ms, 10,000 x
+// n = 24 0.55 -> 0.53 ms, 1,024 x n = 100 2.34 -> 1.64 ms, bitwise the same results.
 //
 // The steps and readings are those of lane_tron.hpp (Algorithm 1 with the TRON ratio test,
 // the step measured in the trust region's norm, and the trapezoid reduction near rounding
@@ -75,6 +81,151 @@ MT_INLINE double wave_max(double v)
     v = max_nan(v, dpp_mov<kDppHalfMirror>(v));
     v = max_nan(v, dpp_mov<kDppMirror>(v));
     return max_nan(max_nan(bcast(v, 0), bcast(v, 16)), max_nan(bcast(v, 32), bcast(v, 48)));
+}
+
+// Row broadcasts read lanes that must be switched on: none of these stands in a condition that
+// differs between lanes. A source written just before takes two wait states.
+
+// value of lane S of each 16-lane row in every lane of the row
+template <int S>
+MT_INLINE double row_bcast(double v)
+{
+    double d;
+    asm volatile("s_nop 1\n\t"
+        "v_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf"
+        : "=v"(d) : "v"(v), "n"(S));
+    return d;
+}
+// d -= (value of q in lane S of the lane's 16-lane row) * m, in one instruction. The broadcast
+// rides on the multiply-add (its source register may have been written just before, which
+// takes two wait states), so a row of a panel's update costs one instruction, not three.
+template <int S>
+MT_INLINE void fnma_row(double &d, double q, double m)
+{
+    asm volatile("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %1, -%2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+        : "+&v"(d) : "v"(q), "v"(m), "n"(S));
+}
+// d0..d3 -= (q in lanes S, S + 1, S + 2, S + 3) * m
+template <int S>
+MT_INLINE void fnma_row4(double &d0, double &d1, double &d2, double &d3, double q, double m)
+{
+    asm volatile("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %4, -%5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %4, -%5 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %4, -%5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %4, -%5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+        : "+&v"(d0), "+&v"(d1), "+&v"(d2), "+&v"(d3)
+        : "v"(q), "v"(m), "n"(S), "n"(S + 1), "n"(S + 2), "n"(S + 3));
+}
+// d += (q in lane S) m0 + (q in lane S + 1) m1 + ..., one after the other
+template <int S>
+MT_INLINE void fma_row4(double &d, double q, double m0, double m1, double m2, double m3)
+{
+    asm volatile("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+        : "+&v"(d)
+        : "v"(q), "v"(m0), "v"(m1), "v"(m2), "v"(m3), "n"(S), "n"(S + 1), "n"(S + 2), "n"(S + 3));
+}
+// d -= (q in lane S) m0, then lane S + D, S + 2 D, S + 3 D
+template <int S, int D>
+MT_INLINE void fnma_row4x(double &d, double q, double m0, double m1, double m2, double m3)
+{
+    asm volatile("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %1, -%2 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, -%3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, -%4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, -%5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+        : "+&v"(d)
+        : "v"(q), "v"(m0), "v"(m1), "v"(m2), "v"(m3), "n"(S), "n"(S + D), "n"(S + 2 * D), "n"(S + 3 * D));
+}
+template <int S>
+MT_INLINE void fma_row(double &d, double q, double m)
+{
+    asm volatile("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+        : "+&v"(d) : "v"(q), "v"(m), "n"(S));
+}
+// d -= (q0 in lane S) m0, then (q1 in lane S) m1: a column pair of a triangular solve, its even
+// column into e and its odd one into o
+template <int S>
+MT_INLINE void fnma_pair(double &e, double &o, double q0, double m0, double q1, double m1)
+{
+    asm volatile("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %2, -%3 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %4, -%5 row_newbcast:%6 row_mask:0xf bank_mask:0xf"
+        : "+&v"(e), "+&v"(o) : "v"(q0), "v"(m0), "v"(q1), "v"(m1), "n"(S));
+}
+// d0..d3 += (q in lanes S, S + 1, S + 2, S + 3) * (m0..m3)
+template <int S>
+MT_INLINE void fma_row4a(double &d0, double &d1, double &d2, double &d3, double q, double m0, double m1, double m2, double m3)
+{
+    asm volatile("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %4, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %4, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %4, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %4, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf"
+        : "+&v"(d0), "+&v"(d1), "+&v"(d2), "+&v"(d3)
+        : "v"(q), "v"(m0), "v"(m1), "v"(m2), "v"(m3), "n"(S), "n"(S + 1), "n"(S + 2), "n"(S + 3));
+}
+
+// Sums of a column C of a triangular solve by columns: p0 and p1 less the products of columns C1
+// .. E - 1 (even ones from p0, odd ones from p1) of the lane's entries t with the pivot row's,
+// which lane C of each 16-lane row holds in q.
+template <int C, int C1, int E>
+MT_INLINE void row_sums(const double (&t)[16], const double (&q)[16], double &p0, double &p1)
+{
+    if constexpr (C1 + 1 < E) {
+        fnma_pair<C>(p0, p1, q[C1], t[C1], q[C1 + 1], t[C1 + 1]);
+        row_sums<C, C1 + 2, E>(t, q, p0, p1);
+    } else if constexpr (C1 < E) {
+        fnma_row<C>(p0, q[C1], t[C1]);  // C1 is even
+    }
+}
+
+// One 16 x 16 diagonal block of a substitution, a row per lane of each 16-lane row: step by step
+// the row's result b dv goes to the others (l: the lane's entries in the block, 0 where it is not
+// to be changed). kUp: from the last row to the first. Four steps at a time, those past the
+// block's `rows` rows left out.
+template <int S, bool kUp>
+MT_INLINE void block_steps(double &b, double dv, const double (&l)[16])
+{
+    constexpr int D = kUp ? -1 : 1, F = kUp ? S + 3 : S;
+    fnma_row<F>(b, b * dv, l[F]);
+    fnma_row<F + D>(b, b * dv, l[F + D]);
+    fnma_row<F + 2 * D>(b, b * dv, l[F + 2 * D]);
+    fnma_row<F + 3 * D>(b, b * dv, l[F + 3 * D]);
+}
+template <bool kUp>
+MT_INLINE void block_solve(double &b, double dv, const double (&l)[16], int rows)
+{
+    if constexpr (kUp) {
+        if (rows > 12) block_steps<12, true>(b, dv, l);
+        if (rows > 8) block_steps<8, true>(b, dv, l);
+        if (rows > 4) block_steps<4, true>(b, dv, l);
+        block_steps<0, true>(b, dv, l);
+    } else {
+        block_steps<0, false>(b, dv, l);
+        if (rows <= 4) return;
+        block_steps<4, false>(b, dv, l);
+        if (rows <= 8) return;
+        block_steps<8, false>(b, dv, l);
+        if (rows <= 12) return;
+        block_steps<12, false>(b, dv, l);
+    }
+}
+// b less the products of 16 results (lane t of each 16-lane row holds result t in y) with l
+template <bool kUp>
+MT_INLINE void block_update(double &b, double y, const double (&l)[16])
+{
+    constexpr int D = kUp ? -1 : 1, F = kUp ? 15 : 0;
+    fnma_row4x<F, D>(b, y, l[F], l[F + D], l[F + 2 * D], l[F + 3 * D]);
+    fnma_row4x<F + 4 * D, D>(b, y, l[F + 4 * D], l[F + 5 * D], l[F + 6 * D], l[F + 7 * D]);
+    fnma_row4x<F + 8 * D, D>(b, y, l[F + 8 * D], l[F + 9 * D], l[F + 10 * D], l[F + 11 * D]);
+    fnma_row4x<F + 12 * D, D>(b, y, l[F + 12 * D], l[F + 13 * D], l[F + 14 * D], l[F + 15 * D]);
 }
 
 // Objective families of the wave kernel. Each holds its own per-lane data and supplies
@@ -231,6 +382,8 @@ struct TronSteps {
     Vec hd;                    // H diagonal (own rows)
     Vec lo, hi, x, g;
     double xs[R];
+    double hc[R];              // H (xs - x) while hc_ok: the accepted Cauchy trial's product
+    bool hc_ok;
     uint64_t lfm[R];           // free set of the last factored pass
     bool has_l;
     double f, delta, alphac;
@@ -295,14 +448,16 @@ struct TronSteps {
         return sig > 0.0 ? sig : 0.0;
     }
 
-    MT_INLINE bool cauchy_trial(double a, double (&xt)[R])
+    // have: the norm test let the product hs = H (xt - x) be formed
+    MT_INLINE bool cauchy_trial(double a, double (&xt)[R], double (&hs)[R], bool &have)
     {
-        double st[R], hs[R];
+        double st[R];
         MT_UNROLL for (int r = 0; r < R; r++) {
             xt[r] = clampf(fma(-a, g[r], x[r]), lo[r], hi[r]);
             st[r] = xt[r] - x[r];
         }
-        if (!(dot(st, st) <= delta * delta)) return false;
+        have = dot(st, st) <= delta * delta;
+        if (!have) return false;
         self().hmul(st, hs);
         double ss[R];
         MT_UNROLL for (int r = 0; r < R; r++) ss[r] = fma(0.5, hs[r], g[r]);
@@ -333,11 +488,16 @@ struct TronSteps {
         int t = 0;
         bool up = false;  // extrapolating: xs holds an acceptable point
         for (;;) {
-            double xt[R];
-            const bool ok = cauchy_trial(at, xt);
+            double xt[R], ht[R];
+            bool have;
+            const bool ok = cauchy_trial(at, xt, ht, have);
             if (up && !ok) break;
             a = at;
-            MT_UNROLL for (int r = 0; r < R; r++) xs[r] = xt[r];
+            hc_ok = have;
+            MT_UNROLL for (int r = 0; r < R; r++) {
+                xs[r] = xt[r];
+                hc[r] = ht[r];
+            }
             if (ok) {
                 up = up || t == 0;
                 if (!up || t == kCauchyMax || !below_last_breakpoint(a)) break;
@@ -423,10 +583,14 @@ struct TronSteps {
             int m = 0;
             MT_UNROLL for (int r = 0; r < R; r++) m += __builtin_popcountll(fm[r]);
             if (m == 0) break;
+            // the first pass starts from the Cauchy point, whose trial has formed this product
             double s[R], rv[R];
-            MT_UNROLL for (int r = 0; r < R; r++) s[r] = xs[r] - x[r];
-            self().hmul(s, rv);
-            MT_UNROLL for (int r = 0; r < R; r++) rv[r] += g[r];
+            if (!hc_ok) {
+                MT_UNROLL for (int r = 0; r < R; r++) s[r] = xs[r] - x[r];
+                self().hmul(s, hc);
+            }
+            hc_ok = false;
+            MT_UNROLL for (int r = 0; r < R; r++) rv[r] = hc[r] + g[r];
             const double shift = self().precond(fm);
             has_l = true;
             MT_UNROLL for (int r = 0; r < R; r++) lfm[r] = fm[r];
@@ -606,7 +770,7 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
     double *Q;                 // with M in global memory: kStage steps of each lane's entries of
                                // L, parked in LDS by the substitutions (slot (t R + r) 64 + lane)
     static constexpr int kStage = 8;
-    double dinv[R];
+    double dinv[R], pv[R];     // the factor's reciprocal pivots and pivots (own rows)
 
     // H_kj (upper triangle, diagonal included) sits at min(j,k) ld + max(j,k) = min(j,k)
     // (ld - 1) + j + k: with blk = M + k + j0 for a block of columns j = j0 + u (u a
@@ -626,9 +790,106 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
         }
     }
 
+    // A copy of v in column n (rows < n), from which every lane reads back the 16 entries its
+    // 16-lane row broadcasts in turn.
+    MT_INLINE void spread(const double (&v)[R]) const
+    {
+        MT_UNROLL for (int r = 0; r < R; r++)
+            if (valid(r)) M[(int)__umul24((unsigned)row(r), (unsigned)ld) + n] = v[r];
+        lds_sync();
+    }
+    MT_INLINE double chunk(int k) const
+    {
+        const int i = 16 * k + (lane & 15);
+        return M[(int)__umul24((unsigned)(i < n ? i : 0), (unsigned)ld) + n];
+    }
+
+    // acc[r][u] = sum over j = u mod 4 of entry(r, j0, u) v_j (j = j0 + u, u a constant), the
+    // columns past the last multiple of 4 in acc[r][0]. A product is one instruction: v_j rides on
+    // it by a row broadcast, 16 columns (what is left of them: 4 at a time) from one copy of v's
+    // entries; with n < 16 the one 16-lane row that has rows holds v itself.
+    template <class E>
+    MT_INLINE void products(const double (&v)[R], E entry, double (&acc)[R][4]) const
+    {
+        MT_UNROLL for (int r = 0; r < R; r++) acc[r][0] = acc[r][1] = acc[r][2] = acc[r][3] = 0.0;
+        const int n4 = n & ~3;
+        int j0 = 0;
+        double q = v[0];
+        if (n >= 16) {
+            spread(v);
+            q = chunk(0);
+#pragma unroll 1
+            for (; j0 + 16 <= n; j0 += 16) {
+                const double vq = q;
+                if (j0 + 16 < n4) q = chunk((j0 >> 4) + 1);
+                MT_UNROLL for (int r = 0; r < R; r++) {
+                    double e[16];
+                    MT_UNROLL for (int u = 0; u < 16; u++) e[u] = entry(r, j0, u);
+                    fma_row4a<0>(acc[r][0], acc[r][1], acc[r][2], acc[r][3], vq, e[0], e[1], e[2], e[3]);
+                    fma_row4a<4>(acc[r][0], acc[r][1], acc[r][2], acc[r][3], vq, e[4], e[5], e[6], e[7]);
+                    fma_row4a<8>(acc[r][0], acc[r][1], acc[r][2], acc[r][3], vq, e[8], e[9], e[10], e[11]);
+                    fma_row4a<12>(acc[r][0], acc[r][1], acc[r][2], acc[r][3], vq, e[12], e[13], e[14], e[15]);
+                }
+            }
+        }
+        if (j0 < n4) {
+            MT_UNROLL for (int r = 0; r < R; r++) {
+                double e[12];
+                MT_UNROLL for (int u = 0; u < 4; u++) e[u] = entry(r, j0, u);
+                if (j0 + 4 < n4) MT_UNROLL for (int u = 4; u < 8; u++) e[u] = entry(r, j0, u);
+                if (j0 + 8 < n4) MT_UNROLL for (int u = 8; u < 12; u++) e[u] = entry(r, j0, u);
+                fma_row4a<0>(acc[r][0], acc[r][1], acc[r][2], acc[r][3], q, e[0], e[1], e[2], e[3]);
+                if (j0 + 4 < n4) fma_row4a<4>(acc[r][0], acc[r][1], acc[r][2], acc[r][3], q, e[4], e[5], e[6], e[7]);
+                if (j0 + 8 < n4) fma_row4a<8>(acc[r][0], acc[r][1], acc[r][2], acc[r][3], q, e[8], e[9], e[10], e[11]);
+            }
+        }
+#pragma unroll 1
+        for (j0 = n4; j0 < n; j0++) {
+            const double vj = this->comp(v, j0);
+            MT_UNROLL for (int r = 0; r < R; r++) acc[r][0] = fma(entry(r, j0, 0), vj, acc[r][0]);
+        }
+    }
+
     // y = H v over the first n rows (H's diagonal read from LDS, as hess() stored it); rows
     // >= n give 0. Four independent accumulators per row; no lane-dependent branches.
     MT_INLINE void hmul(const double (&v)[R], double (&y)[R]) const
+    {
+        if constexpr (kGlobal) {
+            hmul_global(v, y);
+            return;
+        }
+        double acc[R][4];
+        int kk[R];
+        MT_UNROLL for (int r = 0; r < R; r++) kk[r] = row(r) < n ? row(r) : 0;
+        const unsigned ldb = 8u * (unsigned)(ld - 1);
+        products(v, [&](int r, int j0, int u) { return hrd(M + kk[r] + j0, ldb, kk[r], j0 + u, u); }, acc);
+        MT_UNROLL for (int r = 0; r < R; r++)
+            y[r] = valid(r) ? (acc[r][0] + acc[r][1]) + (acc[r][2] + acc[r][3]) : 0.0;
+    }
+
+    // y = A v over the first n rows, A = H's off-diagonal part with diagonal diag (QP4's f
+    // and gradient use Q's diagonal); rows >= n give 0. H's diagonal makes way for the product.
+    template <class D>
+    MT_INLINE void diagonal(const D &d) const
+    {
+        MT_UNROLL for (int r = 0; r < R; r++)
+            if (valid(r)) M[(int)__umul24((unsigned)row(r), (unsigned)(ld + 1))] = d[r];
+    }
+    MT_INLINE void amul(const double (&v)[R], const double (&diag)[R], double (&y)[R]) const
+    {
+        if constexpr (kGlobal) {
+            amul_global(v, diag, y);
+            return;
+        }
+        diagonal(diag);
+        hmul(v, y);
+        diagonal(hd);
+        lds_sync();
+    }
+
+    // the same with M in global memory: a 32-bit index off the wave's uniform base, components
+    // of v by readlane
+    MT_INLINE void hmul_global(const double (&v)[R], double (&y)[R]) const
     {
         double acc[R][4];
         int kk[R];
@@ -659,9 +920,8 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
             y[r] = valid(r) ? (acc[r][0] + acc[r][1]) + (acc[r][2] + acc[r][3]) : 0.0;
     }
 
-    // y = A v over the first n rows, A = H's off-diagonal part with diagonal diag (QP4's f
-    // and gradient use Q's diagonal); rows >= n give 0.
-    MT_INLINE void amul(const double (&v)[R], const double (&diag)[R], double (&y)[R]) const
+
+    MT_INLINE void amul_global(const double (&v)[R], const double (&diag)[R], double (&y)[R]) const
     {
         double acc[R][4];
         int kk[R];
@@ -729,7 +989,8 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
     // False when a pivot of a free column is not positive (the caller then raises alpha).
     MT_INLINE bool chol(const uint64_t (&fm)[R], double alpha)
     {
-        return chol_panels(fm, alpha);
+        if constexpr (kGlobal) return chol_panels(fm, alpha);
+        else return chol_lds(fm, alpha);
     }
 
     // Entry (k, j), k >= j, of H_FF + alpha I with the identity outside F, and 0 above the
@@ -745,81 +1006,174 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
     }
 
     // Factor the 16 columns j0 .. j0 + 15 of S (left in the factor's slots, its diagonal in
-    // column n), each lane holding its rows in registers, left-looking inside the panel and
-    // pipelined by one column. The serial chain per column is kept to: the pivot lane's own
-    // diagonal update, one readlane of the pivot, the reciprocal square root and the scale.
-    // Beside it, the other rows subtract column c - 1 (its entry in row j0 + c read from the
-    // pivot lane), and column c + 1 subtracts the panel's columns before c, reading row
-    // j0 + c + 1 of the factor from LDS at one address in every lane (a broadcast read of
-    // entries final since the last step). Each scaled entry goes straight to its slot in LDS
-    // (one unconditional-path store per column, so the wait for the broadcast reads never
-    // covers it); the pivots are stored once, after the panel.
-    MT_INLINE bool panel_factor(const uint64_t (&fm)[R], int j0)
+    // column n), left-looking, a column at a time. Every 16-lane row holds the panel's own 16 rows
+    // (sv; what stands right of their diagonal is whatever was there and meets only itself), so
+    // that the entries of a pivot row reach every lane by row broadcasts; each lane also holds
+    // its own rows below the panel (t, kBelow). The serial chain per column is the pivot's last
+    // update, its broadcast, the reciprocal square root and the scale; the sums of the next
+    // column up to its last but one term fill the waits. Entries of rows and columns outside F
+    // need no masks: S is the identity there, so they stay exact zeros beside pivots of 1. The
+    // pivots before their square roots go to column n.
+    template <int C, bool kBelow>
+    MT_INLINE void panel_column(double (&sv)[16], double (&t)[R][16], double (&e)[2], double s0, const double (&w0)[R],
+                                double dg, int j0, const int (&irow)[R], double *const (&dst)[R], bool &bad)
     {
-        const int rp = j0 >> 6;  // register slot of the panel's rows
-        double sv[R][16], pv[R];
-        MT_UNROLL for (int r = 0; r < R; r++) {
-            const int i = row(r);
-            pv[r] = 1.0;
-            MT_UNROLL for (int c = 0; c < 16; c++) {
-                const int j = j0 + c;
-                const bool in = i < n && i >= j;
-                const double v = M[in ? (int)__umul24((unsigned)i, (unsigned)ld) + (i == j ? n : j) : 0];
-                sv[r][c] = in ? v : 0.0;
+        if constexpr (C < 16) {
+            if (!kBelow && j0 + C >= n) return;
+            double own = dg;
+            if constexpr (C > 0) own = fma(-sv[C - 1], sv[C - 1], e[0] + e[1]);
+            const double d = row_bcast<C>(own);
+            const double rinv = rsqrt_pos(d);
+            double s = s0, w[R];
+            MT_UNROLL for (int r = 0; r < R; r++) w[r] = w0[r];
+            if constexpr (C > 0) {
+                fnma_row<C>(s, sv[C - 1], sv[C - 1]);
+                if constexpr (kBelow) MT_UNROLL for (int r = 0; r < R; r++) fnma_row<C>(w[r], sv[C - 1], t[r][C - 1]);
             }
-        }
-        // A non-positive free pivot is remembered and reported once the panel is done. Column
-        // c + 1 may lie past n (then it is prepared from row 0 and never used).
-        bool bad = false;
-        MT_UNROLL for (int c = 0; c < 16; c++) {
-            const int j = j0 + c;
-            if (j >= n) break;
-            double pre[16];
-            if (c + 1 < 16) {
-                const int jn = j + 1 < n ? j + 1 : 0;
-                const double *rn = M + __umul24((unsigned)jn, (unsigned)ld) + j0;
-                MT_UNROLL for (int c1 = 0; c1 < c; c1++) pre[c1] = rn[c1];
-            }
-            double own = sv[0][c], prev = c > 0 ? sv[0][c - 1] : 0.0;
-            MT_UNROLL for (int r = 1; r < R; r++) {
-                own = rp == r ? sv[r][c] : own;
-                prev = rp == r ? sv[r][c - (c > 0)] : prev;
-            }
-            if (c > 0) own = fma(-prev, prev, own);  // in the pivot lane: S_jj less L_j,j-1^2
-            const double d = uni(bcast(own, j & 63));
-            if (c > 0) {
-                const double l = bcast(prev, j & 63);
-                MT_UNROLL for (int r = 0; r < R; r++) sv[r][c] = fma(-sv[r][c - 1], l, sv[r][c]);
-            }
-            const bool fj = is_free(fm, j);
-            bad = bad || (fj && !(d > 0.0));
-            const double rinv = fj ? rsqrt_pos(fj ? d : 1.0) : 1.0;  // branch-free
-            const double piv = fj ? d * rinv : 1.0;
-            MT_UNROLL for (int r = 0; r < R; r++) {
-                const int i = row(r);
-                sv[r][c] = (fj && own_free(fm, r)) ? sv[r][c] * rinv : 0.0;
-                pv[r] = i == j ? piv : pv[r];
-                dinv[r] = i == j ? rinv : dinv[r];
-                if (i < n && i > j) M[__umul24((unsigned)i, (unsigned)ld) + j] = sv[r][c];
-            }
-            if (c + 1 < 16) {
+            double sn = 0.0, wn[R];
+            if constexpr (C + 1 < 16) {
+                double p1 = 0.0;
+                sn = sv[C + 1];
+                row_sums<C + 1, 0, C>(sv, sv, sn, p1);
+                sn = sn + p1;
                 MT_UNROLL for (int r = 0; r < R; r++) {
-                    double p0 = sv[r][c + 1], p1 = 0.0;
-                    MT_UNROLL for (int c1 = 0; c1 < c; c1++) {
-                        if (c1 & 1) p1 = fma(-sv[r][c1], pre[c1], p1);
-                        else p0 = fma(-sv[r][c1], pre[c1], p0);
+                    wn[r] = 0.0;
+                    if constexpr (kBelow) {
+                        double q1 = 0.0;
+                        wn[r] = t[r][C + 1];
+                        row_sums<C + 1, 0, C>(t[r], sv, wn[r], q1);
+                        wn[r] = wn[r] + q1;
                     }
-                    sv[r][c + 1] = p0 + p1;
                 }
             }
-            sync();
+            if constexpr (C > 0) e[(C - 1) & 1] = fma(-sv[C - 1], sv[C - 1], e[(C - 1) & 1]);
+            const int j = j0 + C;
+            bad = bad || !(d > 0.0);
+            M[(int)__umul24((unsigned)j, (unsigned)ld) + n] = d;
+            sv[C] = s * rinv;
+            MT_UNROLL for (int r = 0; r < R; r++) {
+                if constexpr (kBelow) t[r][C] = w[r] * rinv;
+                if (irow[r] > j) dst[r][C] = kBelow ? t[r][C] : sv[C];
+            }
+            panel_column<C + 1, kBelow>(sv, t, e, sn, wn, dg, j0, irow, dst, bad);
+        }
+    }
+
+    // 16 consecutive entries of a row of M, those past column n - 1 replaced by others (columns
+    // of a partial panel that are not there)
+    MT_INLINE void row16(const double *p, int cols, double (&v)[16]) const
+    {
+        if (cols >= 16) MT_UNROLL for (int c = 0; c < 16; c++) v[c] = p[c];
+        else MT_UNROLL for (int c = 0; c < 16; c++) v[c] = p[c < cols ? c : 0];
+    }
+
+    template <bool kBelow>
+    MT_INLINE bool panel_factor(int j0)
+    {
+        const int il = lane & 15, cols = n - j0;
+        const int ip = il < cols ? j0 + il : j0;
+        const double *pr = M + (int)__umul24((unsigned)ip, (unsigned)ld);
+        double sv[16], t[R][16], e[2], w0[R];
+        const double dg = pr[n];
+        if constexpr (kBelow) MT_UNROLL for (int c = 0; c < 16; c++) sv[c] = pr[j0 + c];
+        else row16(pr + j0, cols, sv);
+        int irow[R];
+        double *dst[R];
+        MT_UNROLL for (int r = 0; r < R; r++) {
+            // the lane's row to store: its own where the panel's rows hold for all lanes, or
+            // where that is one of the panel's rows
+            const int i = row(r);
+            const bool in = i < n && (kBelow || (i >= j0));
+            irow[r] = in ? i : -1;
+            dst[r] = M + (int)__umul24((unsigned)(in ? i : 0), (unsigned)ld) + j0;
+            if constexpr (kBelow) MT_UNROLL for (int c = 0; c < 16; c++) t[r][c] = dst[r][c];
+            w0[r] = kBelow ? t[r][0] : 0.0;
+        }
+        e[0] = dg;
+        e[1] = 0.0;
+        bool bad = false;
+        panel_column<0, kBelow>(sv, t, e, sv[0], w0, dg, j0, irow, dst, bad);
+        lds_sync();
+        return __builtin_amdgcn_readfirstlane((int)bad) == 0;
+    }
+
+    // S's starting values at the 16 x 16 block of row k0, column j0 (lane: row lq + 4 v, column
+    // lr): A = H_FF + alpha I with the identity outside F. Entries outside the lower part of the
+    // first n rows are not kept.
+    MT_INLINE void block_start(const uint64_t (&fm)[R], int k0, int j0, double alpha, double (&e)[4]) const
+    {
+        const int lr = lane & 15, lq = lane >> 4;
+        const int jb = j0 + lr, jbk = jb < n ? jb : n - 1;
+        const uint32_t fj = (uint32_t)(mask_word(fm, j0 >> 6) >> (j0 & 63)) >> lr;
+        const uint32_t fk = (fj & 1u) ? (uint32_t)(mask_word(fm, k0 >> 6) >> (k0 & 63)) >> lq : 0u;
+        const double *p = M + (int)__umul24((unsigned)jbk, (unsigned)ld);
+        MT_UNROLL for (int v = 0; v < 4; v++) {
+            const int i0 = k0 + lq + 4 * v, i = i0 < n ? i0 : n - 1;
+            const double h = p[i];
+            e[v] = ((fk >> (4 * v)) & 1u) ? h : 0.0;
+            if (k0 == j0) e[v] = lq + 4 * v == lr ? ((fj & 1u) ? h + alpha : 1.0) : e[v];
+        }
+    }
+    MT_INLINE uint64_t mask_word(const uint64_t (&fm)[R], int q) const
+    {
+        uint64_t t = fm[0];
+        MT_UNROLL for (int r = 1; r < R; r++) t = q == r ? fm[r] : t;
+        return t;
+    }
+
+    // Blocked left-looking factorisation in panels of 16 columns. For the panel starting at
+    // column j0, the matrix cores form S = A[j0:n, panel] - L[j0:n, 0:j0] L[panel, 0:j0]^T,
+    // 16 x 16 blocks by 16 x 16 x 4 FP64 products (operands read from LDS once, no
+    // broadcasts); then panel_factor.
+    // Lane layout of the 16 x 16 x 4 FP64 product: A(i, k) in lane i + 16 k, B(k, j) in lane
+    // j + 16 k, C(i, j) in lane j + 16 (i mod 4), element i / 4 of the lane's four. Rows and
+    // columns past n read row n - 1; their results are not kept.
+    MT_INLINE bool chol_lds(const uint64_t (&fm)[R], double alpha)
+    {
+        typedef double d4 __attribute__((ext_vector_type(4)));
+        const int lr = lane & 15, lq = lane >> 4;
+#pragma unroll 1
+        for (int j0 = 0; j0 < n; j0 += 16) {
+            const int jb = j0 + lr, jbk = jb < n ? jb : n - 1;
+            const double *rb = M + (int)__umul24((unsigned)jbk, (unsigned)ld) + lq;
+#pragma unroll 1
+            for (int k0 = j0; k0 < n; k0 += 16) {
+                const int kak = k0 + lr < n ? k0 + lr : n - 1;
+                const double *ra = M + (int)__umul24((unsigned)kak, (unsigned)ld) + lq;
+                double e[4];
+                block_start(fm, k0, j0, alpha, e);
+                d4 acc0, acc1 = {0.0, 0.0, 0.0, 0.0};
+                MT_UNROLL for (int v = 0; v < 4; v++) acc0[v] = e[v];
+#pragma unroll 1
+                for (int q0 = 0; q0 < j0; q0 += 16) {
+                    double a[4], b[4];
+                    MT_UNROLL for (int v = 0; v < 4; v++) {
+                        a[v] = -ra[q0 + 4 * v];
+                        b[v] = rb[q0 + 4 * v];
+                    }
+                    acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0], b[0], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1], b[1], acc1, 0, 0, 0);
+                    acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[2], b[2], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[3], b[3], acc1, 0, 0, 0);
+                }
+                MT_UNROLL for (int v = 0; v < 4; v++) {
+                    const int k = k0 + lq + 4 * v;
+                    // S below the diagonal into the factor's slots, its diagonal into column n
+                    if (k < n && jb < n && k >= jb)
+                        M[(int)__umul24((unsigned)k, (unsigned)ld) + (k == jb ? n : jb)] = acc0[v] + acc1[v];
+                }
+            }
+            lds_sync();
+            if (!(j0 + 16 < n ? panel_factor<true>(j0) : panel_factor<false>(j0))) return false;
         }
         MT_UNROLL for (int r = 0; r < R; r++) {
-            const int i = row(r);
-            if (i >= j0 && i < j0 + 16 && i < n) M[__umul24((unsigned)i, (unsigned)ld) + n] = pv[r];
+            const double d = M[(int)__umul24((unsigned)(valid(r) ? row(r) : 0), (unsigned)ld) + n];
+            const double rinv = rsqrt_pos(d);
+            const bool fr = valid(r) && own_free(fm, r);
+            dinv[r] = fr ? rinv : 1.0;
+            pv[r] = fr ? d * rinv : 1.0;
         }
-        sync();
-        return !bad;
+        return true;
     }
 
     // The same panel step with M in global memory, in two passes that
@@ -904,14 +1258,7 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
         return !bad;
     }
 
-    // Blocked left-looking factorisation in panels of 16 columns. For the panel starting at
-    // column j0, the matrix cores form S = A[j0:n, panel] - L[j0:n, 0:j0] L[panel, 0:j0]^T,
-    // 16 x 16 blocks by 16 x 16 x 4 FP64 products (operands read from LDS once, no
-    // broadcasts); then each lane factors its rows of S in registers, column by column, with
-    // the pivot and the panel's own factor entries broadcast by readlane. One wave barrier per
-    // phase instead of one per column.
-    // Lane layout of the 16 x 16 x 4 FP64 product: A(i, k) in lane i + 16 k, B(k, j) in lane
-    // j + 16 k, C(i, j) in lane j + 16 (i mod 4), element i / 4 of the lane's four.
+    // The same with M in global memory, the operands of eight chunks loaded per trip to L2.
     MT_INLINE bool chol_panels(const uint64_t (&fm)[R], double alpha)
     {
         typedef double d4 __attribute__((ext_vector_type(4)));
@@ -929,18 +1276,15 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
                 // rows past n read row 0 (always present) and use 0
                 const bool ain = ka < n, bin = jb < n;
                 int q0 = 0;
-                if constexpr (kGlobal) {
-                    // operands from L2: eight chunks' loads in flight per round trip
-                    for (; q0 + 32 <= j0; q0 += 32) {
-                        double av[8], bv[8];
-                        MT_UNROLL for (int u = 0; u < 8; u++) {
-                            av[u] = ra[q0 + 4 * u];
-                            bv[u] = rb[q0 + 4 * u];
-                        }
-                        MT_UNROLL for (int u = 0; u < 8; u += 2) {
-                            acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(ain ? -av[u] : 0.0, bin ? bv[u] : 0.0, acc0, 0, 0, 0);
-                            acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(ain ? -av[u + 1] : 0.0, bin ? bv[u + 1] : 0.0, acc1, 0, 0, 0);
-                        }
+                for (; q0 + 32 <= j0; q0 += 32) {
+                    double av[8], bv[8];
+                    MT_UNROLL for (int u = 0; u < 8; u++) {
+                        av[u] = ra[q0 + 4 * u];
+                        bv[u] = rb[q0 + 4 * u];
+                    }
+                    MT_UNROLL for (int u = 0; u < 8; u += 2) {
+                        acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(ain ? -av[u] : 0.0, bin ? bv[u] : 0.0, acc0, 0, 0, 0);
+                        acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(ain ? -av[u + 1] : 0.0, bin ? bv[u + 1] : 0.0, acc1, 0, 0, 0);
                     }
                 }
                 for (; q0 + 8 <= j0; q0 += 8) {
@@ -960,11 +1304,7 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
                 }
             }
             sync();
-            if constexpr (kGlobal) {
-                if (!panel_factor_split(fm, j0)) return false;
-            } else {
-                if (!panel_factor(fm, j0)) return false;
-            }
+            if (!panel_factor_split(fm, j0)) return false;
         }
         return true;
     }
@@ -998,7 +1338,8 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
             if (i < n) {
                 const double v = fabs(hd[r]);
                 const double piv = own_free(fm, r) ? sqrt(v > beta ? v : beta) : 1.0;
-                M[__umul24((unsigned)i, (unsigned)ld) + n] = piv;
+                if constexpr (kGlobal) M[__umul24((unsigned)i, (unsigned)ld) + n] = piv;
+                pv[r] = piv;
                 dinv[r] = 1.0 / piv;
             }
         }
@@ -1012,6 +1353,75 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
         double v = b[0] * dinv[0];
         MT_UNROLL for (int r = 1; r < R; r++) v = (j >> 6) == r ? b[r] * dinv[r] : v;
         return bcast(v, j & 63);
+    }
+
+    // The steps of a substitution in blocks of 16 rows, kUp false: L y = b, true: L^T y = b (then
+    // from the last block to the first). The block's 16-lane row runs its 16 steps by row
+    // broadcasts, its results go to column n, and every row still to come subtracts their 16
+    // columns. b keeps unscaled residuals.
+    template <bool kUp>
+    MT_INLINE void substitute(double (&b)[R]) const
+    {
+        const int il = lane & 15, nb = (n + 15) >> 4;
+        double dl[16];
+#pragma unroll 1
+        for (int q = 0; q < nb; q++) {
+            const int blk = kUp ? nb - 1 - q : q, sl = blk >> 2, j0 = 16 * blk;
+            if (q == 0 || (blk & 3) == (kUp ? 3 : 0)) {
+                // the lane's entries in the diagonal block of its own row in this slot
+                // (rows past n, whose residuals are 0, stay 0 and pass 0 on)
+                const int i = lane + 64 * sl, ik = i < n ? i : n - 1, i0 = i - il;
+                const int from = i < n ? il : kUp ? 16 : 0;
+                // byte offsets along the row (or down the column), kept inside the array
+                const unsigned step = kUp ? 8u * (unsigned)ld : 8u;
+                const unsigned at = 8u * (kUp ? __umul24((unsigned)i0, (unsigned)ld) + (unsigned)ik : __umul24((unsigned)ik, (unsigned)ld) + (unsigned)i0);
+                const unsigned last = at + (unsigned)(n - 1 - i0) * step;
+                MT_UNROLL for (int t = 0; t < 16; t++) {
+                    const unsigned o = at + (unsigned)t * step;
+                    const double v = *(const double *)((const char *)M + (o < last ? o : last));
+                    dl[t] = (kUp ? t > from : t < from) ? v : 0.0;
+                }
+            }
+            double tb = b[0], dv = dinv[0];
+            MT_UNROLL for (int r = 1; r < R; r++) {
+                tb = sl == r ? b[r] : tb;
+                dv = sl == r ? dinv[r] : dv;
+            }
+            const int own = lane + 64 * sl;
+            dv = own < n ? dv : 1.0;
+            const bool more = q + 1 < nb;
+            // entries of the rows still to come, loaded ahead of the block's steps
+            double l[R][16];
+            if (more) {
+                MT_UNROLL for (int r = 0; r < R; r++) {
+                    if (R > 1 && (kUp ? r > sl : r < sl)) continue;
+                    const int ik = valid(r) ? row(r) : 0;
+                    MT_UNROLL for (int t = 0; t < 16; t++) {
+                        if (kUp) l[r][t] = M[(int)__umul24((unsigned)(j0 + t < n ? j0 + t : n - 1), (unsigned)ld) + ik];
+                        else l[r][t] = M[(int)__umul24((unsigned)ik, (unsigned)ld) + j0 + t];
+                    }
+                }
+            }
+            double t = tb;
+            block_solve<kUp>(t, dv, dl, n - j0);
+            const bool mine = (lane >> 4) == (blk & 3);
+            tb = mine ? t : tb;
+            MT_UNROLL for (int r = 0; r < R; r++) b[r] = sl == r ? tb : b[r];
+            if (!more) break;
+            const double y = tb * dv;
+            if (mine && own < n) M[(int)__umul24((unsigned)own, (unsigned)ld) + n] = y;
+            lds_sync();
+            const int iy = j0 + il;
+            const double y0 = M[(int)__umul24((unsigned)(iy < n ? iy : 0), (unsigned)ld) + n];
+            const double yq = iy < n ? y0 : 0.0;
+            MT_UNROLL for (int r = 0; r < R; r++) {
+                if (R > 1 && (kUp ? r > sl : r < sl)) continue;
+                double u = b[r];
+                block_update<kUp>(u, yq, l[r]);
+                const bool left = valid(r) && (kUp ? row(r) < j0 : row(r) >= j0 + 16);
+                b[r] = left ? u : b[r];
+            }
+        }
     }
 
     // L y = b in place (b zero outside the factored set stays zero). Each row keeps its
@@ -1041,22 +1451,7 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
                 }
             }
         } else {
-            // the lane's row of L from column 0 (a row past n reads row 0, its update masked:
-            // its index is taken as -1)
-            const double *lr[R];
-            int ii[R];
-            MT_UNROLL for (int r = 0; r < R; r++) {
-                const int i = row(r);
-                ii[r] = i < n ? i : -1;
-                lr[r] = M + (int)__umul24((unsigned)(i < n ? i : 0), (unsigned)ld);
-            }
-            for (int j = 0; j < n; j++) {
-                const double yj = owner_scaled(b, j);
-                MT_UNROLL for (int r = 0; r < R; r++) {
-                    const double l = lr[r][j];
-                    b[r] = fma(-(j < ii[r] ? l : 0.0), yj, b[r]);
-                }
-            }
+            substitute<false>(b);
         }
         MT_UNROLL for (int r = 0; r < R; r++) b[r] = valid(r) ? b[r] * dinv[r] : b[r];
     }
@@ -1081,18 +1476,7 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
                 }
             }
         } else {
-            // the lane's column of L (entry j at j ld + i; a row past n reads column 0, and
-            // is never above a step)
-            const double *lc[R];
-            MT_UNROLL for (int r = 0; r < R; r++) lc[r] = M + (row(r) < n ? row(r) : 0);
-            const unsigned ldb = 8u * (unsigned)ld;
-            for (int j = n - 1; j >= 0; j--) {
-                const double yj = owner_scaled(b, j);
-                MT_UNROLL for (int r = 0; r < R; r++) {
-                    const double l = *(const double *)((const char *)lc[r] + (unsigned)j * ldb);
-                    b[r] = fma(-(row(r) < j ? l : 0.0), yj, b[r]);
-                }
-            }
+            substitute<true>(b);
         }
         MT_UNROLL for (int r = 0; r < R; r++) b[r] = valid(r) ? b[r] * dinv[r] : b[r];
     }
@@ -1100,6 +1484,21 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
     MT_INLINE double step_norm(const double (&s)[R]) const
     {
         if (!has_l) return sqrt(dot(s, s));
+        // t = L^T s: t_i = L_ii s_i + sum_{k > i} L_ki s_k, in four partial sums by k mod 4
+        // (entries of rows not below i count as exact zeros)
+        if constexpr (!kGlobal) {
+            double acc[R][4], t[R];
+            int kk[R];
+            MT_UNROLL for (int r = 0; r < R; r++) kk[r] = valid(r) ? row(r) : n;
+            products(s, [&](int r, int k0, int u) {
+                const bool in = kk[r] < k0 + u;
+                const double l = M[(int)__umul24((unsigned)(k0 + u), (unsigned)ld) + (in ? kk[r] : 0)];
+                return in ? l : 0.0;
+            }, acc);
+            MT_UNROLL for (int r = 0; r < R; r++)
+                t[r] = valid(r) ? fma(pv[r], s[r], (acc[r][0] + acc[r][1]) + (acc[r][2] + acc[r][3])) : 0.0;
+            return sqrt(dot(t, t));
+        }
         // t = L^T s: t_i = L_ii s_i + sum_{k > i} L_ki s_k (the pivot L_ii sits in column n), in
         // four independent partial sums, four broadcasts and loads at a time (entries of rows
         // not below i are read as exact zeros, no selects)
