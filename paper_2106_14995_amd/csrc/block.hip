@@ -4,9 +4,8 @@
 
 namespace {
 
-// kEu: waves per SIMD the registers are budgeted for (4: two workgroups of eight waves per CU)
-template <int R, int W, bool kGlobal, int kEu>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(kEu))) void block_kernel(LaneArgs a)
+template <int R, int W, bool kGlobal>
+__global__ __launch_bounds__(64 * W) void block_kernel(LaneArgs a)
 {
     extern __shared__ double block_smem[];
     const int64_t t = blockIdx.x;
@@ -50,17 +49,17 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(kEu))) v
     }
 }
 
-template <int R, int W, bool kGlobal, int kEu>
+template <int R, int W, bool kGlobal>
 void launch(const LaneArgs &a, int nmax, hipStream_t st)
 {
     const size_t lds = mt::BlockTron<R, W, kGlobal>::lds_bytes(nmax);
-    hipLaunchKernelGGL((block_kernel<R, W, kGlobal, kEu>), dim3((unsigned)a.count), dim3(64 * W), lds, st, a);
+    hipLaunchKernelGGL((block_kernel<R, W, kGlobal>), dim3((unsigned)a.count), dim3(64 * W), lds, st, a);
 }
 
-template <int R, int W, bool kGlobal, int kEu>
+template <int R, int W, bool kGlobal>
 void prepare()
 {
-    (void)hipFuncSetAttribute((const void *)block_kernel<R, W, kGlobal, kEu>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    (void)hipFuncSetAttribute((const void *)block_kernel<R, W, kGlobal>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)mt::BlockTron<R, W, kGlobal>::lds_bytes(64 * R));
 }
 
@@ -69,12 +68,14 @@ void prepare()
 void mt_launch_block(const LaneArgs &a, int nmax, hipStream_t st)
 {
     if (a.count <= 0) return;
-    if (nmax <= 256) launch<4, 8, true, 2>(a, nmax, st);
-    else launch<8, 8, true, 2>(a, nmax, st);
+    if (nmax <= kLdsMaxN) launch<2, 8, false>(a, nmax, st);
+    else if (nmax <= 256) launch<4, 8, true>(a, nmax, st);
+    else launch<8, 8, true>(a, nmax, st);
 }
 
 void mt_prepare_block_kernels()
 {
-    prepare<4, 8, true, 2>();
-    prepare<8, 8, true, 2>();
+    prepare<2, 8, false>();
+    prepare<4, 8, true>();
+    prepare<8, 8, true>();
 }

@@ -241,7 +241,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void
 // From n_max = kWaveBigN on the LDS request already limits residency to about two waves per SIMD,
 // and a batch of up to two waves per SIMD of the chip has no use for a third.
 constexpr int kWaveBigN = 48;
-constexpr int64_t kWaveFewCount = 2048;
+constexpr int kCus = 256;
+constexpr int64_t kWaveFewCount = 2 * 4 * kCus;
+constexpr size_t kCuLds = 160 * 1024;
 
 static size_t wave_lds_bytes(int nmax) { return sizeof(double) * (size_t)nmax * (size_t)((nmax + 1) | 1); }
 
@@ -283,12 +285,18 @@ static void launch_wave_fam(tron_family fam, const LaneArgs &a, int nmax, hipStr
         if (nmax <= 64) launch_wave<WaveFamHS45M<1>>(a, nmax, st);
         else launch_wave<WaveFamHS45M<2>>(a, nmax, st);
     } else {
+        // n in 65..128: a workgroup of eight waves per instance, unless at least two waves of the
+        // wavefront kernel fit a CU's LDS (nmax <= 100) and the batch has more instances than the
+        // chip CUs: then they make better use of a CU together. 256 instances, wavefront kernel
+        // against workgroup: n = 80 0.54 / 0.45 ms, n = 100 0.83 / 0.59 ms, n = 128 1.12 / 0.67 ms;
+        // 1,024: n = 80 0.90 / 0.95 ms, n = 100 1.61 / 1.92 ms, n = 128 3.83 / 2.17 ms.
+        const bool alone = 2 * wave_lds_bytes(nmax) > kCuLds;
         // beyond LDS one wave per instance leaves most of the chip idle at the batch sizes that
         // fit its memory, and walks its matrices through L2 alone: a workgroup per instance
         // takes 3.5-6 times less (512 instances: n = 200 16.5 -> 4.2 ms, n = 512 151 -> 25.7 ms;
         // three instances of n = 129 3.8 -> 1.1 ms)
         if (nmax <= 64) launch_wave<WaveFamQP4<1>>(a, nmax, st);
-        else if (nmax <= kLdsMaxN) launch_wave<WaveFamQP4<2>>(a, nmax, st);
+        else if (nmax <= kLdsMaxN && !alone && a.count > kCus) launch_wave<WaveFamQP4<2>>(a, nmax, st);
         else mt_launch_block(a, nmax, st);
     }
 }
