@@ -180,17 +180,17 @@ __device__ void reduce_parts64(const double *part_primal, int64_t np, const doub
 // Outputs: x, radius and Cauchy step in the state, f, status and iterations per branch.
 // With prev_resid, one workgroup past the branches' reduces the residual parts the previous
 // iteration's bus kernel left (nothing writes them before this kernel ends).
-__global__ __launch_bounds__(kBlock) void branch_kernel(Net n, double *s, mt::Options opt, double *fo,
+__global__ __launch_bounds__(kBlock) void branch_kernel(Net n, double *s, mt::Options opt, WaveShare share, double *fo,
                                                         int32_t *status, int32_t *iters,
                                                         const double *part_primal, const double *part_dual,
                                                         double *prev_resid)
 {
-    if (blockIdx.x == (n.L + kBlock - 1) / kBlock) {
+    if (blockIdx.x == (n.L + share.per - 1) / share.per) {
         reduce_parts64(part_primal, n.B, part_dual, n.B, n.rho, prev_resid);
         return;
     }
-    const int64_t l = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (l >= n.L) return;
+    bool own;
+    const int64_t l = mt_wave_item((int)threadIdx.x, share, n.L, own);
     View v = split(s, n.G, n.L, n.B);
     const double rho = n.rho;
     const int i = n.br_from[l], j = n.br_to[l];
@@ -215,6 +215,7 @@ __global__ __launch_bounds__(kBlock) void branch_kernel(Net n, double *s, mt::Op
         st.x[k] = x[k];
     }
     const int32_t rc = st.solve(opt, v.del[l], v.alp[l]);
+    if (!own) return;
     MT_UNROLL for (int k = 0; k < 6; k++) x[k] = st.x[k];
     fo[l] = st.f;
     status[l] = rc;
@@ -611,13 +612,14 @@ extern "C" tron_err admm_step(admm *a, int32_t iters, double *d_resid, void *str
     // spread over more CUs; each wave's parameter blocks take 36 x 64 doubles of LDS
     const size_t lds = sizeof(double) * mt::BR6::kLdsDoubles * kBlock;
     double *part_primal = a->d_part, *part_dual = a->d_part + n.B;
+    const WaveShare share = mt_wave_share(n.L, kBlock);
     for (int32_t it = 0; it < iters; it++) {
         if (it == 0 && n.G > 0)
             hipLaunchKernelGGL(gen_kernel, dim3(grid_for(n.G)), dim3(kBlock), 0, st, n, a->d_state);
         // the previous iteration's residuals are reduced by one more workgroup of this launch
         double *prev = (it > 0 && d_resid) ? d_resid + 2 * (int64_t)(it - 1) : nullptr;
-        hipLaunchKernelGGL(branch_kernel, dim3(grid_for(n.L) + (prev ? 1u : 0u)), dim3(kBlock), lds, st, n,
-                           a->d_state, opt, a->d_f, a->d_status, a->d_iters, (const double *)part_primal,
+        hipLaunchKernelGGL(branch_kernel, dim3((unsigned)((n.L + share.per - 1) / share.per) + (prev ? 1u : 0u)), dim3(kBlock), lds, st, n,
+                           a->d_state, opt, share, a->d_f, a->d_status, a->d_iters, (const double *)part_primal,
                            (const double *)part_dual, prev);
         hipLaunchKernelGGL(bus_kernel, dim3(grid_for((int64_t)n.B * kBusLanes)), dim3(kBlock), 0, st, n, a->d_state, part_primal,
                            part_dual, (int)(it + 1 < iters));

@@ -8,8 +8,9 @@
 template <class Fam, int N, int G>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void group_kernel(LaneArgs a)
 {
-    const int64_t t = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
-    if (t >= a.count) return;  // whole groups leave together
+    bool own;  // the same in all lanes of a group
+    const int64_t t = mt_wave_item((int)(threadIdx.x & 63) / G, a.share, a.count, own);
+    if (t < 0) return;
     const int64_t b = a.index ? (int64_t)a.index[t] : t;
     const int n = a.nper ? a.nper[b] : a.n_uniform;
     const int64_t po = a.poff ? a.poff[b] : b * (int64_t)a.psize;
@@ -32,6 +33,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
     const double din = a.opt.warm ? a.state[b] : 0.0;
     const double ain = a.opt.warm ? a.state[a.batch + b] : 0.0;
     const int32_t st = s.solve(a.opt, din, ain);
+    if (!own) return;
     double *xo = a.x + vo;
     MT_UNROLL for (int r = 0; r < S::R; r++)
         if (s.row(r) < n) xo[s.row(r)] = s.x[r];
@@ -52,9 +54,11 @@ template <class Fam, int N, int G>
 static void launch_group(const LaneArgs &a, hipStream_t st)
 {
     const int blk = a.lane_block == 64 ? 64 : 256;
-    const int64_t threads = a.count * G;
-    const unsigned grid = (unsigned)((threads + blk - 1) / blk);
-    if (grid) hipLaunchKernelGGL((group_kernel<Fam, N, G>), dim3(grid), dim3(blk), 0, st, a);
+    LaneArgs s = a;
+    s.share = mt_wave_share(a.count, 64 / G);
+    const int64_t per = (int64_t)s.share.per * (blk / 64);
+    const unsigned grid = (unsigned)((a.count + per - 1) / per);
+    if (grid) hipLaunchKernelGGL((group_kernel<Fam, N, G>), dim3(grid), dim3(blk), 0, st, s);
 }
 
 lane_launch_fn mt_group_launcher(tron_family fam, int N, int G)

@@ -9,9 +9,9 @@
 // the kernel accepts; with one wave per SIMD either way, the register budget is the same.
 constexpr int kLaneBlock = 256;
 
-// Solve instance b in the calling lane.
+// Solve instance b in the calling lane; own: store its results (else the lane repeats another's).
 template <class F, int N>
-__device__ __forceinline__ void lane_solve(const LaneArgs &a, int64_t b)
+__device__ __forceinline__ void lane_solve(const LaneArgs &a, int64_t b, bool own)
 {
     const int n = a.nper ? a.nper[b] : a.n_uniform;
     const int64_t po = a.poff ? a.poff[b] : b * (int64_t)a.psize;
@@ -30,6 +30,7 @@ __device__ __forceinline__ void lane_solve(const LaneArgs &a, int64_t b)
     const double din = a.opt.warm ? a.state[b] : 0.0;
     const double ain = a.opt.warm ? a.state[a.batch + b] : 0.0;
     const int32_t st = s.solve(a.opt, din, ain);
+    if (!own) return;
     double *xo = a.x + vo;
     MT_UNROLL for (int i = 0; i < N; i++)
         if (i < n) xo[i] = s.x[i];
@@ -47,16 +48,20 @@ __device__ __forceinline__ void lane_solve(const LaneArgs &a, int64_t b)
 template <class F, int N>
 __global__ __launch_bounds__(kLaneBlock) void lane_kernel(LaneArgs a)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= a.count) return;
-    lane_solve<F, N>(a, a.index ? (int64_t)a.index[t] : t);
+    bool own;
+    const int64_t t = mt_wave_item((int)threadIdx.x & 63, a.share, a.count, own);
+    if (t < 0) return;
+    lane_solve<F, N>(a, a.index ? (int64_t)a.index[t] : t, own);
 }
 
 template <class F, int N>
 static void launch_lane(const LaneArgs &a, hipStream_t st)
 {
     const int blk = a.lane_block == 64 ? 64 : kLaneBlock;
-    const unsigned grid = (unsigned)((a.count + blk - 1) / blk);
+    LaneArgs s = a;
+    s.share = mt_wave_share(a.count, 64);
+    const int64_t per = (int64_t)s.share.per * (blk / 64);
+    const unsigned grid = (unsigned)((a.count + per - 1) / per);
     const size_t lds = sizeof(double) * (size_t)F::kLdsDoubles * (size_t)blk;
-    if (grid) hipLaunchKernelGGL((lane_kernel<F, N>), dim3(grid), dim3(blk), lds, st, a);
+    if (grid) hipLaunchKernelGGL((lane_kernel<F, N>), dim3(grid), dim3(blk), lds, st, s);
 }

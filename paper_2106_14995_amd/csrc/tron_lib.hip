@@ -108,11 +108,12 @@ struct AlArgs {
     int32_t outer_max;
 };
 
-__global__ __launch_bounds__(kLaneBlock) void al_kernel(LaneArgs a, AlArgs al)
+// one wavefront per workgroup, spread and repeated like the lane kernels' (mt_wave_share)
+__global__ __launch_bounds__(64) void al_kernel(LaneArgs a, AlArgs al)
 {
     constexpr int N = 8;
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= a.count) return;
+    bool own;
+    const int64_t b = mt_wave_item((int)threadIdx.x, a.share, a.count, own);
     mt::LaneTron<mt::BR8L, N> s;
     double *prm = al.params + 40 * b;
     s.fam.load(prm, N);
@@ -145,6 +146,7 @@ __global__ __launch_bounds__(kLaneBlock) void al_kernel(LaneArgs a, AlArgs al)
         if (v > al.decrease * vprev) s.fam.rhoh = mt::dmin(s.fam.rhoh * al.rho_growth, al.rho_max);
         vprev = v;
     }
+    if (!own) return;
     double *xo = a.x + N * b;
     MT_UNROLL for (int i = 0; i < N; i++) xo[i] = s.x[i];
     a.f[b] = s.f;
@@ -460,22 +462,24 @@ static void prepare_pool_kernels(int bytes)
 }
 
 // Lane packs: the instances with n <= 8 in packs of 64 of one size (a wave each; -1 pads a
-// pack), every size in one launch. pack_n[k] is the size of pack k.
+// pack, and its lane repeats the pack's first instance, see mt_wave_share), every size in one
+// launch. pack_n[k] is the size of pack k.
 template <template <int> class FamT>
 __global__ __launch_bounds__(64) void lane_pack_kernel(LaneArgs a, const int32_t *pack_n)
 {
-    const int64_t t = (int64_t)blockIdx.x * 64 + threadIdx.x;
-    const int32_t b = a.index[t];
-    if (b < 0) return;
+    const int64_t t = (int64_t)blockIdx.x * 64;
+    const int32_t mine = a.index[t + threadIdx.x];
+    const bool own = mine >= 0;
+    const int32_t b = own ? mine : a.index[t];
     switch (pack_n[blockIdx.x]) {
-    case 1: lane_solve<FamT<1>, 1>(a, b); break;
-    case 2: lane_solve<FamT<2>, 2>(a, b); break;
-    case 3: lane_solve<FamT<3>, 3>(a, b); break;
-    case 4: lane_solve<FamT<4>, 4>(a, b); break;
-    case 5: lane_solve<FamT<5>, 5>(a, b); break;
-    case 6: lane_solve<FamT<6>, 6>(a, b); break;
-    case 7: lane_solve<FamT<7>, 7>(a, b); break;
-    default: lane_solve<FamT<8>, 8>(a, b); break;
+    case 1: lane_solve<FamT<1>, 1>(a, b, own); break;
+    case 2: lane_solve<FamT<2>, 2>(a, b, own); break;
+    case 3: lane_solve<FamT<3>, 3>(a, b, own); break;
+    case 4: lane_solve<FamT<4>, 4>(a, b, own); break;
+    case 5: lane_solve<FamT<5>, 5>(a, b, own); break;
+    case 6: lane_solve<FamT<6>, 6>(a, b, own); break;
+    case 7: lane_solve<FamT<7>, 7>(a, b, own); break;
+    default: lane_solve<FamT<8>, 8>(a, b, own); break;
     }
 }
 
@@ -1145,8 +1149,9 @@ extern "C" tron_err tron_al_solve(tron_batch *h, const tron_al_options *opt, dou
     a.psize = 40;
     a.opt = dev_options(h->opt);
     AlArgs al{d_params, d_outer, d_viol, o.ctol, o.rho_growth, o.decrease, o.rho_max, o.outer_max};
-    const unsigned grid = (unsigned)((h->batch + kLaneBlock - 1) / kLaneBlock);
-    hipLaunchKernelGGL(al_kernel, dim3(grid), dim3(kLaneBlock), 0, (hipStream_t)stream, a, al);
+    a.share = mt_wave_share(h->batch, 64);
+    const unsigned grid = (unsigned)((h->batch + a.share.per - 1) / a.share.per);
+    hipLaunchKernelGGL(al_kernel, dim3(grid), dim3(64), 0, (hipStream_t)stream, a, al);
     HIP_TRY(hipGetLastError());
     return TRON_OK;
 }
