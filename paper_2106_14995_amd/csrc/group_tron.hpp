@@ -32,10 +32,14 @@ namespace mt {
 MT_INLINE long long d2ll(double v) { return __double_as_longlong(v); }
 MT_INLINE double ll2d(long long v) { return __longlong_as_double(v); }
 
-// Cross-lane operations inside aligned groups of G lanes.
-template <int G>
+// Cross-lane operations inside aligned groups of G lanes. kTwin: a group of 8 takes a whole
+// 16-lane row and its upper eight lanes do what the lower eight do, so that a broadcast is one
+// row broadcast instead of one per half.
+template <int G, bool kTwin = false>
 struct Grp {
     static_assert(G == 1 || G == 2 || G == 4 || G == 8 || G == 16, "group width");
+    static_assert(!kTwin || G == 8, "a group of 8 in a row of 16");
+    static constexpr int kLanes = kTwin ? 16 : G;  // lanes it takes
 
     // the value of group lane S, in every lane of the group
     template <int S>
@@ -47,7 +51,7 @@ struct Grp {
             return dpp_mov<S | (S << 2) | ((2 + S) << 4) | ((2 + S) << 6)>(v);
         } else if constexpr (G == 4) {
             return dpp_mov<S * 0x55>(v);
-        } else if constexpr (G == 8) {
+        } else if constexpr (G == 8 && !kTwin) {
             // lanes 0..7 of each row take the row's lane S, lanes 8..15 its lane 8 + S
             const long long a = __builtin_amdgcn_update_dpp(0ll, d2ll(v), 0x150 + S, 0xF, 0x3, false);
             return ll2d(__builtin_amdgcn_update_dpp(a, d2ll(v), 0x158 + S, 0xF, 0xC, false));
@@ -94,7 +98,7 @@ struct Grp {
     static MT_INLINE uint32_t bits(bool p)
     {
         const uint64_t b = __ballot(p);
-        const int base = (int)(threadIdx.x & 63) & ~(G - 1);
+        const int base = (int)(threadIdx.x & 63) & ~(kLanes - 1);
         return (uint32_t)(b >> base) & (G == 32 ? 0xFFFFFFFFu : ((1u << G) - 1u));
     }
     static MT_INLINE bool any(bool p) { return bits(p) != 0u; }
@@ -251,11 +255,11 @@ struct GBR6 {
 // ------------------------------------------------------------------------------------
 // The solver for one group.
 // ------------------------------------------------------------------------------------
-template <class Fam, int N, int G>
+template <class Fam, int N, int G, bool kTwin = false>
 struct GroupTron {
     static_assert(N >= 1 && N <= 16, "the group solver holds n <= 16");
     static constexpr int R = (N + G - 1) / G;
-    using X = Grp<G>;
+    using X = Grp<G, kTwin>;
     Fam fam;
     int n;                 // the instance's size (<= N); rows at or past n are fixed padding
     int k;                 // lane within the group
@@ -303,6 +307,14 @@ struct GroupTron {
     }
     MT_INLINE void hmul(const double (&v)[R], double (&out)[R]) const
     {
+        if constexpr (kTwin && R == 1 && N == 8) {
+            // the broadcasts ride on the multiply-adds (a 16-lane row is on as a whole)
+            double s = 0.0;
+            fma_row4<0>(s, v[0], fam.H(*this, 0, 0), fam.H(*this, 0, 1), fam.H(*this, 0, 2), fam.H(*this, 0, 3));
+            fma_row4<4>(s, v[0], fam.H(*this, 0, 4), fam.H(*this, 0, 5), fam.H(*this, 0, 6), fam.H(*this, 0, 7));
+            out[0] = s;
+            return;
+        }
         double va[N];
         all(v, va);
         MT_UNROLL for (int r = 0; r < R; r++) {
