@@ -472,10 +472,8 @@ struct GroupTron {
             const bool owner = k == j % G;
             MT_UNROLL for (int c = j + 1; c < N; c++) {
                 const double lcj = X::from(lrow[c / G][j], c % G);
-                MT_UNROLL for (int r = 0; r < R; r++) {
-                    const double u = fma(-lrow[r][j], lcj, lrow[r][c]);
-                    lrow[r][c] = ge(r, c) ? u : lrow[r][c];
-                }
+                // (entries right of the diagonal take it too; nothing reads them)
+                MT_UNROLL for (int r = 0; r < R; r++) lrow[r][c] = fma(-lrow[r][j], lcj, lrow[r][c]);
                 lcol[j / G][c] = owner ? lcj : lcol[j / G][c];
             }
         }
