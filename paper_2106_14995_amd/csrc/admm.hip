@@ -612,7 +612,10 @@ extern "C" tron_err admm_step(admm *a, int32_t iters, double *d_resid, void *str
     // spread over more CUs; each wave's parameter blocks take 36 x 64 doubles of LDS
     const size_t lds = sizeof(double) * mt::BR6::kLdsDoubles * kBlock;
     double *part_primal = a->d_part, *part_dual = a->d_part + n.B;
-    const WaveShare share = mt_wave_share(n.L, kBlock);
+    // A wave per CU while that leaves a wave at most a quarter of its lanes (launch_lane has the
+    // same rule). Measured, packed / a wave per CU: 25 iterations on 3,000 branches 822 / 784 us
+    // (a wave per SIMD alike), 15 on 4,100 457 / 451, on 6,000 559 / 587, on 9,000 832 / 867.
+    const WaveShare share = mt_wave_share(n.L, kBlock, n.L <= 16 * (kSimds / 4) ? kSimds / 4 : 1);
     for (int32_t it = 0; it < iters; it++) {
         if (it == 0 && n.G > 0)
             hipLaunchKernelGGL(gen_kernel, dim3(grid_for(n.G)), dim3(kBlock), 0, st, n, a->d_state);

@@ -59,7 +59,13 @@ static void launch_lane(const LaneArgs &a, hipStream_t st)
 {
     const int blk = a.lane_block == 64 ? 64 : kLaneBlock;
     LaneArgs s = a;
-    s.share = mt_wave_share(a.count, 64);
+    // The branch solve is short (3.5 iterations) and its first pass over the code and the
+    // parameters' loads are much of it, so it goes on one wave per CU rather than per SIMD, and
+    // not apart at all once a quarter of the lanes of those would have an own instance. Measured,
+    // packed / a wave per CU / per SIMD: 1,500 instances 48.8 / 47.3 / 49.0 us; 4,096 50.6 / 49.3 /
+    // 51.2; 9,000 50.6 / 51.8 / 52.8.
+    const int waves = F::kSpread ? kSimds : a.count <= 16 * (kSimds / 4) ? kSimds / 4 : 1;
+    s.share = mt_wave_share(a.count, 64, waves);
     const int64_t per = (int64_t)s.share.per * (blk / 64);
     const unsigned grid = (unsigned)((a.count + per - 1) / per);
     const size_t lds = sizeof(double) * (size_t)F::kLdsDoubles * (size_t)blk;

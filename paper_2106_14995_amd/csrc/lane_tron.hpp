@@ -86,7 +86,8 @@ struct Options {
 };
 
 // ------------------------------------------------------------------------------------
-// Problem families. Each provides: pad (value of padded variables), load(p, n),
+// Problem families. Each provides: pad (value of padded variables), kSpread (a small batch goes
+// on one wave per SIMD, see launch_lane), load(p, n),
 // fg(x, g) -> f (caches what hess needs), hess(x) (at the point of the last fg),
 // H(i, j) (compile-time i, j).
 // ------------------------------------------------------------------------------------
@@ -96,6 +97,7 @@ template <int N>
 struct QP4 {
     static constexpr int T = N * (N + 1) / 2;
     static constexpr double pad = 0.0;
+    static constexpr bool kSpread = true;
     static constexpr int kLdsDoubles = 0;  // per lane, in the lane kernel's dynamic LDS
     double q[T];
     double c[N];
@@ -139,6 +141,7 @@ template <int N>
 struct HS45M {
     static constexpr int T = N * (N + 1) / 2;
     static constexpr double pad = 1.0;
+    static constexpr bool kSpread = true;
     static constexpr int kLdsDoubles = 0;
     double h[T];
     MT_INLINE void load(const double *__restrict__, int) {}
@@ -187,6 +190,7 @@ struct BR6T {
     static constexpr int N = 6;
     static constexpr int T = 21;
     static constexpr double pad = 0.0;
+    static constexpr bool kSpread = false;
     static constexpr int kLdsDoubles = kLds ? 36 : 0;
     double prm_r[kLds ? 1 : 36];
     double cth, sth;       // cos, sin of th_i - th_j at the last fg point
@@ -355,6 +359,7 @@ struct BR8L {
     static constexpr int N = 8;
     static constexpr int T = 36;
     static constexpr double pad = 0.0;
+    static constexpr bool kSpread = true;
     static constexpr int kLdsDoubles = 0;
     BR6R b6;               // the BR6 part; its Hessian block also receives the limit terms
     double smax2, lam[2], rhoh;

@@ -45,7 +45,7 @@ __host__ __device__ inline int mt_block_ld(int n) { return 16 * (((n + 15) / 16)
 __host__ __device__ inline int64_t mt_block_slot_doubles(int nmax) { return (int64_t)nmax * mt_block_ld(nmax); }
 
 // Instances per wavefront of the kernels that hold several (at most `most`: 64 lanes or 64 / G
-// groups): as many as leave every SIMD of the card one wavefront, so that a batch too small to
+// groups): as many as leave every SIMD of the card one wavefront (or `waves` in all), so that a batch too small to
 // fill the card is spread instead of packed. A wavefront runs every branch that any of its
 // instances takes and lasts as long as its slowest one, so fewer instances end sooner; more
 // than one wavefront per SIMD does not pay (the branch solves of 16,384 instances: 54 us at one,
@@ -59,9 +59,9 @@ __host__ __device__ inline int64_t mt_block_slot_doubles(int nmax) { return (int
 // 60 -> 59 -> 52 us; 1,000 of n = 6 65 -> 89 -> 58; 512 multiplier loops 832 -> 676 -> 533,
 // 16,384 1,340 -> 1,500 -> 1,210; 25 ADMM iterations on 3,000 branches 834 -> 1,400 -> 790.
 constexpr int kSimds = 1024;
-inline WaveShare mt_wave_share(int64_t count, int most)
+inline WaveShare mt_wave_share(int64_t count, int most, int waves = kSimds)
 {
-    int64_t per = (count + kSimds - 1) / kSimds;
+    int64_t per = (count + waves - 1) / waves;
     per = per < 1 ? 1 : per < most ? per : most;
     return {(int32_t)per, (int32_t)((65535 + per) / per)};
 }

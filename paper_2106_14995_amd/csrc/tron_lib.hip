@@ -13,6 +13,8 @@
 #include <string>
 #include <vector>
 
+#include <type_traits>
+
 #include "lane_kernels.hpp"
 #include "lane_tron.hpp"
 #include "tron.h"
@@ -240,11 +242,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void
     wave_body<Fam, true>(a);
 }
 
-// From n_max = kWaveBigN on the LDS request already limits residency to about two waves per SIMD,
-// and a batch of up to two waves per SIMD of the chip has no use for a third.
-constexpr int kWaveBigN = 48;
 constexpr int kCus = 256;
-constexpr int64_t kWaveFewCount = 2 * 4 * kCus;
+// Which of the two builds takes a batch of instances up to n = 64. The build for two waves per SIMD:
+//   from n = 44 on, where the LDS holds little more than that (12,000 of n = 44, three waves
+//     against two: 1,160 / 1,074 us; of n = 47 1,326 / 1,142; n = 40 still 1,000 / 1,009);
+//   where it needs no more rounds over the chip than the other, up to 2,048 instances and from
+//     3,073 to 4,096 (4,000 of n = 9 162 / 148 us, of n = 16 187 / 169; 3,000 of n = 16 139 / 149);
+//   for the quartics of n = 17 to 24 beyond that (12,000 of n = 17 554 / 520 us, of n = 24 636 / 620;
+//     n = 16 391 / 401, n = 28 680 / 675, n = 36 925 / 959).
+template <class Fam>
+static bool two_waves(int nmax, int64_t count)
+{
+    constexpr int64_t two = 2 * 4 * kCus, three = 3 * 4 * kCus;
+    if (nmax >= 44 || (count + two - 1) / two == (count + three - 1) / three) return true;
+    return std::is_same<Fam, mt::WaveFamQP4<1>>::value && nmax > 16 && nmax <= 24 && count > three;
+}
 constexpr size_t kCuLds = 160 * 1024;
 
 static size_t wave_lds_bytes(int nmax) { return sizeof(double) * (size_t)nmax * (size_t)((nmax + 1) | 1); }
@@ -259,7 +271,7 @@ static void launch_wave(const LaneArgs &a, int nmax, hipStream_t st)
     if constexpr (Fam::R > 1) {
         hipLaunchKernelGGL((wave_kernel_big<Fam>), dim3((unsigned)a.count), dim3(64), lds, st, a);
     } else {
-        if (nmax >= kWaveBigN || a.count <= kWaveFewCount)
+        if (two_waves<Fam>(nmax, a.count))
             hipLaunchKernelGGL((wave_kernel_big<Fam>), dim3((unsigned)a.count), dim3(64), lds, st, a);
         else
             hipLaunchKernelGGL((wave_kernel<Fam>), dim3((unsigned)a.count), dim3(64), lds, st, a);
