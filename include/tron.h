@@ -114,7 +114,8 @@ tron_err tron_batch_create(tron_batch **out, tron_family family, int64_t batch,
                            void *stream);
 
 /* Launch plan of a handle: instances with n <= lane_max_n are solved one per GPU lane (a
- * kernel per exact n); larger ones one per wavefront, grouped into buckets by the first of
+ * kernel per exact n); larger ones one per wavefront (of the quartic family, those of n > 128
+ * and some of n > 64 one per workgroup), grouped into buckets by the first of
  * `edges` (increasing, <= 128) that holds them, with LDS sized for that edge. Buckets run
  * concurrently on `streams` streams; lane kernels use workgroups of lane_block (64 or 256).
  * pool_waves > 0 selects the persistent size-bucketed form instead (section 4.1, a single
@@ -172,10 +173,11 @@ tron_err tron_autotune(tron_family family, int64_t batch, const int32_t *n_host,
 /* Solve every instance (Algorithm 1 per instance). d_x0 (read) and d_x (written) may be the
  * same buffer for an in-place warm start. d_f (batch doubles), d_status and d_iters (batch
  * int32 each) are written. d_params, d_lo, d_hi are read only. Bounds may be +-inf.
- * Instances with n <= 8 are solved one per GPU lane, larger ones one per wavefront (up to
- * n = 128 with the Hessian and factor in LDS, beyond that in a global-memory workspace of
- * n ((n+1)|1) doubles per instance, rounded up to n = 256 or 512, that the handle allocates
- * at creation); the size buckets run concurrently on the handle's own streams, joined back
+ * Instances with n <= 8 are solved one per GPU lane, larger ones one per wavefront or, of the
+ * quartic family above n = 64, one per workgroup (up to n = 128 with the Hessian and factor in
+ * LDS, beyond that with the factor in a global-memory workspace of n rows of n rounded up to an
+ * odd number of 16 doubles, n rounded up to 256 or 512, or of n ((n+1)|1) doubles where that is
+ * not to be had, that the handle allocates at creation); the size buckets run concurrently on the handle's own streams, joined back
  * into `stream`.
  * Errors: INVALID (null pointers), DEVICE (launch or capture failure). */
 tron_err tron_batch_solve(tron_batch *h, const double *d_params, const double *d_lo,
@@ -239,7 +241,7 @@ tron_err tron_batch_destroy(tron_batch *h);
  * graph capture, tight serving loops, harnesses that forbid hipMalloc). One cold-start
  * solve of `batch` instances that all have size n, with the same kernels and results as
  * tron_batch_create(n_uniform = n) + tron_batch_solve: instances with n <= 8 one per GPU
- * lane, larger ones one per wavefront. The solve's working memory (per-instance radius and
+ * lane, larger ones one per wavefront or workgroup. The solve's working memory (per-instance radius and
  * Cauchy step length, 16 bytes each, and for n > 128 the matrix workspace of
  * n ((n+1)|1) doubles per instance) lives in a fixed device array of the library,
  * tron_noalloc_scratch_bytes() = 64 MiB on every device the call runs on, held until the

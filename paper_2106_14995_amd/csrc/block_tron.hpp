@@ -9,6 +9,12 @@
 // (four accumulators by column index mod 4 in products, two by panel chunk in the matrix-core
 // updates, even and odd columns inside a panel), so results do not depend on W.
 //
+// What bounds it: up to n = 256 the trips to L2 and the serial steps (pivots of a panel's
+// diagonal block, the substitutions' 16-row blocks) at one workgroup per CU, since 256
+// registers per lane leave two waves per SIMD; at n = 512 the traffic past L2 (47 GB in 13.4 ms
+// for 256 instances, 3.5 TB/s; matrix cores busy 15 %). Against one wave per instance: 512 x n =
+// 200 16.1 -> 3.7 ms, 512 x n = 512 157 -> 23.7 ms.
+//
 // Where the matrices live:
 //   kGlobal false  H (upper triangle with diagonal) and L (strict lower triangle) share one
 //                  LDS array of n rows, odd stride ld > n, as in wave_tron.hpp; pivots and

@@ -4,8 +4,8 @@
 // lower triangle of the Hessian, the packed Cholesky factor and the CG vectors are
 // fixed-size arrays indexed only by compile-time constants after unrolling, so they are
 // registers (the branch family alone keeps its 36 parameters in the workgroup's LDS, see
-// BR6T). 64 instances share a wave and 4 waves a CU; there are no cross-lane operations at
-// all (the paper's warp-per-problem reductions, section 5.1, become plain per-lane sums).
+// BR6T). Up to 64 instances share a wave (fewer in a small batch, see mt_wave_share) and 4 waves
+// a CU; there are no cross-lane operations at all (the paper's warp-per-problem reductions, section 5.1, become plain per-lane sums).
 //
 // Algorithm 1 (section 3) per lane, with the readings of the method that the paper leaves
 // to the TRON method it cites:
