@@ -62,8 +62,9 @@ static void launch_group(const LaneArgs &a, hipStream_t st)
     if constexpr (G == 8) {
         // Up to four instances per wavefront (4,096 of them) groups of 8 leave half the lanes
         // without an instance: each group then takes a row of 16. Measured, calls of 256 quartics
-        // of n = 8 back to back: 36.9 -> 32.2 us (30.0 with the factorisation's selects gone); one of 4,096 with its synchronisation: 66 -> 61. With
-        // more instances it would take twice the wavefronts (16,384: eight groups in each, 88 us).
+        // of n = 8 back to back: 36.9 -> 32.2 us (30.0 with the factorisation's selects gone); one
+        // of 4,096 with its synchronisation: 66 -> 61 us. With more instances it would take twice
+        // the wavefronts.
         if (s.share.per <= 4) {
             hipLaunchKernelGGL((group_kernel<Fam, N, 8, true>), dim3(grid), dim3(blk), 0, st, s);
             return;
