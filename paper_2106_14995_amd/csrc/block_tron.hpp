@@ -82,9 +82,11 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
     static constexpr int oU = oF + 2;                             // tiles / panel / matrix array
     static constexpr int kTile = 64 * 65;
     static constexpr int kU = 2 * kTile > kRows * 17 ? 2 * kTile : kRows * 17;  // kGlobal
+    // (a last panel's steps read 16 entries of a row where fewer are left: up to 15 doubles past
+    // the matrix array, which no result depends on)
     static constexpr size_t lds_bytes(int nmax)
     {
-        return sizeof(double) * (size_t)(oU + (kGlobal ? kU : nmax * ((nmax + 1) | 1)));
+        return sizeof(double) * (size_t)(oU + (kGlobal ? kU : nmax * ((nmax + 1) | 1) + 16));
     }
 
     // what the matrix steps need
@@ -625,7 +627,7 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
             }
         }
         const int sl = (j0 >> 6) + k.w;
-        if (64 * sl >= n || 64 * sl + 63 < j0 + 16) return;
+        if (j0 + 16 >= n || 64 * sl >= n || 64 * sl + 63 < j0 + 16) return;
         const int i = 64 * sl + lane;
         const bool in = i >= j0 + 16 && i < n;
         double t[16], q[16];
