@@ -73,6 +73,12 @@ void mt_launch_block(const LaneArgs &a, int nmax, hipStream_t st)
     else launch<8, 8, true>(a, nmax, st);
 }
 
+size_t mt_block_lds_bytes(int nmax)
+{
+    if (nmax <= kLdsMaxN) return mt::BlockTron<2, 8, false>::lds_bytes(nmax);
+    return nmax <= 256 ? mt::BlockTron<4, 8, true>::lds_bytes(nmax) : mt::BlockTron<8, 8, true>::lds_bytes(nmax);
+}
+
 void mt_prepare_block_kernels()
 {
     prepare<2, 8, false>();

@@ -575,7 +575,7 @@ extern "C" tron_err tron_server_submit(tron_server *s, int64_t batch, const int3
         if (r->n[i] > kLdsMaxN)
             return mt_fail(TRON_ERR_UNSUPPORTED, "instance %lld: n = %d above the server's limit of %d",
                            (long long)i, r->n[i], kLdsMaxN);
-        if (r->n[i] > 8) lds += mt_wave_lds_bytes(wave_nmax_of(r->n[i]));
+        if (r->n[i] > 8) lds += mt_wave_lds_bytes(s->fam, wave_nmax_of(r->n[i]), batch);
         nsum += r->n[i];
         psum += ps;
     }

@@ -88,12 +88,14 @@ lane_launch_fn mt_lane_launcher(tron_family fam, int N);
 // n <= nmax (nmax <= kLdsMaxN: LDS sized for nmax; larger nmax: a.ws must hold a.count
 // slots of a.ws_stride >= mt_wave_matrix_doubles(nmax) doubles).
 void mt_launch_wave(tron_family fam, const LaneArgs &a, int nmax, hipStream_t st);
-// The workgroup-per-instance kernel of the quartic family for kLdsMaxN < n <= nmax (a.ws as
-// above).
+// The workgroup-per-instance kernel of the quartic family for n <= nmax (nmax <= kLdsMaxN: LDS
+// sized for nmax; larger nmax: a.ws as above), and the LDS bytes of one instance.
 void mt_launch_block(const LaneArgs &a, int nmax, hipStream_t st);
+size_t mt_block_lds_bytes(int nmax);
 void mt_prepare_block_kernels();
-// LDS bytes the wave kernel uses for one instance of size n (its bucket's footprint).
-size_t mt_wave_lds_bytes(int nmax);
+// LDS bytes of one instance of a bucket of `count` instances with n <= nmax (nmax <= kLdsMaxN), on
+// whichever kernel mt_launch_wave gives the bucket.
+size_t mt_wave_lds_bytes(tron_family fam, int nmax, int64_t count);
 // Make the wave kernels and the BR6 lane kernel accept their largest LDS request (once per
 // process and device).
 void mt_prepare_wave_kernels();

@@ -285,6 +285,22 @@ static void launch_wave_global(const LaneArgs &a, hipStream_t st)
     hipLaunchKernelGGL((wave_kernel_global<Fam>), dim3((unsigned)a.count), dim3(64), global_lds_bytes<Fam>(), st, a);
 }
 
+// Whether `count` instances with n <= nmax run on a workgroup of eight waves each (without a
+// workspace up to kLdsMaxN).
+//   n in 65..128: unless at least two waves of the wavefront kernel fit a CU's LDS (nmax <= 100)
+//     and the batch has more instances than the chip CUs: then they make better use of a CU
+//     together. 256 instances, wavefront kernel against workgroup: n = 80 0.54 / 0.45 ms, n = 100
+//     0.83 / 0.59 ms, n = 128 1.12 / 0.67 ms; 1,024: n = 80 0.90 / 0.95 ms, n = 100 1.61 / 1.92 ms,
+//     n = 128 3.83 / 2.17 ms.
+//   beyond LDS always: one wave per instance leaves most of the chip idle at the batch sizes that
+//     fit its memory, and walks its matrices through L2 alone (block_tron.hpp has the figures).
+static bool on_workgroup(tron_family fam, int nmax, int64_t count)
+{
+    if (fam != TRON_FAMILY_QP4 || nmax <= 64) return false;
+    const bool alone = 2 * wave_lds_bytes(nmax) > kCuLds;
+    return nmax > kLdsMaxN || alone || count <= kCus;
+}
+
 // the wave kernel of the family for instances with n <= nmax
 static void launch_wave_fam(tron_family fam, const LaneArgs &a, int nmax, hipStream_t st)
 {
@@ -299,19 +315,9 @@ static void launch_wave_fam(tron_family fam, const LaneArgs &a, int nmax, hipStr
         if (nmax <= 64) launch_wave<WaveFamHS45M<1>>(a, nmax, st);
         else launch_wave<WaveFamHS45M<2>>(a, nmax, st);
     } else {
-        // n in 65..128: a workgroup of eight waves per instance, unless at least two waves of the
-        // wavefront kernel fit a CU's LDS (nmax <= 100) and the batch has more instances than the
-        // chip CUs: then they make better use of a CU together. 256 instances, wavefront kernel
-        // against workgroup: n = 80 0.54 / 0.45 ms, n = 100 0.83 / 0.59 ms, n = 128 1.12 / 0.67 ms;
-        // 1,024: n = 80 0.90 / 0.95 ms, n = 100 1.61 / 1.92 ms, n = 128 3.83 / 2.17 ms.
-        const bool alone = 2 * wave_lds_bytes(nmax) > kCuLds;
-        // beyond LDS one wave per instance leaves most of the chip idle at the batch sizes that
-        // fit its memory, and walks its matrices through L2 alone: a workgroup per instance
-        // takes 3.5-6 times less (512 instances: n = 200 16.5 -> 4.2 ms, n = 512 151 -> 25.7 ms;
-        // three instances of n = 129 3.8 -> 1.1 ms)
-        if (nmax <= 64) launch_wave<WaveFamQP4<1>>(a, nmax, st);
-        else if (nmax <= kLdsMaxN && !alone && a.count > kCus) launch_wave<WaveFamQP4<2>>(a, nmax, st);
-        else mt_launch_block(a, nmax, st);
+        if (on_workgroup(fam, nmax, a.count)) mt_launch_block(a, nmax, st);
+        else if (nmax <= 64) launch_wave<WaveFamQP4<1>>(a, nmax, st);
+        else launch_wave<WaveFamQP4<2>>(a, nmax, st);
     }
 }
 
@@ -544,7 +550,10 @@ void mt_launch_wave(tron_family fam, const LaneArgs &a, int nmax, hipStream_t st
 {
     launch_wave_fam(fam, a, nmax, st);
 }
-size_t mt_wave_lds_bytes(int nmax) { return wave_lds_bytes(nmax); }
+size_t mt_wave_lds_bytes(tron_family fam, int nmax, int64_t count)
+{
+    return on_workgroup(fam, nmax, count) ? mt_block_lds_bytes(nmax) : wave_lds_bytes(nmax);
+}
 void mt_prepare_wave_kernels()
 {
     using namespace mt;

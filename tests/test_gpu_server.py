@@ -119,6 +119,28 @@ def test_admission_under_a_tight_budget(T):
     srv.close()
 
 
+@pytest.mark.parametrize("family,charge", [(W.QP4, 154912), (W.HS45M, 132096)])
+def test_lds_account_is_the_kernels_request(T, family, charge):
+    """An instance of n in 65..128 is charged what its kernel asks for: the matrix array of
+    n = 128 for the wavefront kernel (HS45M), and with it the vectors, the panel block and the
+    last panel's reach for the workgroup kernel (QP4)."""
+    count = 2000
+    bt = W.qp4_batch(4, 100, config_id=130) if family == W.QP4 else W.hs45m_batch(4, 100)
+    srv = T.Server(family, hbm_budget=1 << 30, lds_budget=1 << 40)
+    rep = lambda a: np.tile(a, count // 4)
+    t = srv.submit(rep(bt.n), rep(bt.params), rep(bt.lo), rep(bt.hi), rep(bt.x0))
+    seen = 0
+    while seen == 0:
+        done = srv.poll(t) == 2
+        seen = srv.stats()["lds_inflight"]
+        assert seen or not done, "finished before it was seen in flight"
+    assert seen == count * charge
+    srv.wait(t)
+    assert np.all(srv.result(t)["status"] == 0)
+    assert srv.stats()["lds_inflight"] == 0
+    srv.close()
+
+
 def test_sizes_above_the_lds_limit_are_refused(T):
     bt = W.qp4_batch(2, 200, config_id=101)
     srv = T.Server(W.QP4)
