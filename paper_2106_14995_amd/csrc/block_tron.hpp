@@ -414,23 +414,23 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
         return s;
     }
 
-    // a, b: the two panels' blocks of this wave (CNT of them) less their products with the
+    // a, b: the two panels' blocks of this wave (CNT or one fewer) less their products with the
     // columns before j0. The panels' own rows are read by every wave: in the workspace form they
     // go through LDS, panel by panel, 16 rows of a column side by side (two columns span the
     // banks once); a wave's A operands come straight from the workspace, 16 columns' worth in
     // flight while another 16 are used. Rows past n read row n - 1; their results are not kept.
     template <int CNT>
-    static MT_INLINE void panel_products(const Ctx &k, int j0, Sum (&a)[kMost], Sum (&b)[kMost])
+    static MT_INLINE void panel_products(const Ctx &k, int j0, int cnt, Sum (&a)[kMost], Sum (&b)[kMost])
     {
+        const bool all = cnt == CNT;  // this wave has CNT blocks, else one fewer
         const int n = k.n, ld = k.ld, lane = k.lane, lr = lane & 15, lq = lane >> 4;
         lds_double *Bs = k.L0 + oU;
-        constexpr int kC = CNT > 0 ? CNT : 1;
-        uint32_t oa[kC];
+        uint32_t oa[CNT];
         MT_UNROLL for (int t = 0; t < CNT; t++) {
             const int i0 = j0 + 16 * (k.w + W * t) + lr, i = i0 < n ? i0 : n - 1;
             oa[t] = kGlobal ? (uint32_t)(lq * ld + i) * 8u : (uint32_t)(i * ld + lq);
         }
-        struct Ops { double a[kC][4]; };
+        struct Ops { double a[CNT][4]; };
         auto fetch = [&](int q, Ops &o) {
             MT_UNROLL for (int v = 0; v < 4; v++)
                 MT_UNROLL for (int t = 0; t < CNT; t++) {
@@ -441,12 +441,17 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
         };
         // the products of 16 columns; p1, p2: this lane's entries of the panels' rows
         auto use = [&](const Ops &o, const lds_double *p1, const lds_double *p2, int step) {
+            double b1[4], b2[4];
             MT_UNROLL for (int v = 0; v < 4; v++) {
-                const double b1 = p1[v * step], b2 = p2[v * step];
-                MT_UNROLL for (int t = 0; t < CNT; t++) {
+                b1[v] = p1[v * step];
+                b2[v] = p2[v * step];
+            }
+            MT_UNROLL for (int t = 0; t < CNT; t++) {
+                if (t == CNT - 1 && !all) continue;
+                MT_UNROLL for (int v = 0; v < 4; v++) {
                     const double m = -o.a[t][v];
-                    a[t].v[v & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(m, b1, a[t].v[v & 1], 0, 0, 0);
-                    b[t].v[v & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(m, b2, b[t].v[v & 1], 0, 0, 0);
+                    a[t].v[v & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(m, b1[v], a[t].v[v & 1], 0, 0, 0);
+                    b[t].v[v & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(m, b2[v], b[t].v[v & 1], 0, 0, 0);
                 }
             }
         };
@@ -481,7 +486,7 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
                 fetch(qb + 16, y);
                 __syncthreads();
                 const lds_double *p1 = Bs + lane, *p2 = p1 + 16 * kStage;  // column lq of four, row lr
-                if constexpr (CNT > 0) {
+                if (CNT > 1 || all) {
 #pragma unroll 1
                     for (int q = 0; q < qn; q += 32) {
                         use(x, p1 + 16 * q, p2 + 16 * q, 64);
@@ -684,11 +689,13 @@ struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
                     b[t] = block_start(k, k0, j0 + 16, fk, fw, h2, alpha);
                 }
             }
-            if (kMost >= 4 && blocks > 3 * W) panel_products<kMost >= 4 ? 4 : 0>(k, j0, a, b);
-            else if (kMost >= 3 && blocks > 2 * W) panel_products<kMost >= 3 ? 3 : 0>(k, j0, a, b);
-            else if (kMost >= 2 && blocks > W) panel_products<kMost >= 2 ? 2 : 0>(k, j0, a, b);
-            else if (blocks > 0) panel_products<1>(k, j0, a, b);
-            else panel_products<0>(k, j0, a, b);
+            // The form is the one the first wave needs, in all waves: its barriers must not stand in
+            // a branch that waves take differently.
+            const int most = ((k.n - j0 + 15) >> 4) + W - 1, cnt = (blocks + W - 1) / W;
+            if (kMost >= 4 && most >= 4 * W) panel_products<kMost >= 4 ? 4 : 1>(k, j0, cnt, a, b);
+            else if (kMost >= 3 && most >= 3 * W) panel_products<kMost >= 3 ? 3 : 1>(k, j0, cnt, a, b);
+            else if (kMost >= 2 && most >= 2 * W) panel_products<kMost >= 2 ? 2 : 1>(k, j0, cnt, a, b);
+            else panel_products<1>(k, j0, cnt, a, b);
             MT_UNROLL for (int t = 0; t < kMost; t++)
                 if (blocks > W * t) block_store(k, j0 + 16 * (k.w + W * t), j0, a[t]);
 #pragma unroll 1
