@@ -55,16 +55,21 @@ static void launch_group(const LaneArgs &a, hipStream_t st)
 {
     const int blk = a.lane_block == 64 ? 64 : 256;
     LaneArgs s = a;
-    s.share = mt_wave_share(a.count, 64 / G);
+    // The builds for n <= 16 spill, and every wavefront more brings its scratch traffic along: these
+    // are spread over fewer. Quartics of n = 16, groups of 8, packed (before) / on up to 128 wavefronts / on
+    // up to 1,024, rows of 16: 256 instances 541 / 419 / 494 us, 1,000 531 / 499 / 879; groups of
+    // 16, packed / up to 256 / up to 1,024: 256 instances 270 / 214 / 215 us, 1,000 266 / 253 / 421.
+    s.share = mt_wave_share(a.count, 64 / G, N <= 8 ? kSimds : G == 16 ? kSimds / 4 : kSimds / 8);
     const int64_t per = (int64_t)s.share.per * (blk / 64);
     const unsigned grid = (unsigned)((a.count + per - 1) / per);
     if (!grid) return;
-    if constexpr (G == 8) {
+    if constexpr (G == 8 && N <= 8) {
         // Up to four instances per wavefront (4,096 of them) groups of 8 leave half the lanes
-        // without an instance: each group then takes a row of 16. Measured, calls of 256 quartics
-        // of n = 8 back to back: 36.9 -> 32.2 us (30.0 with the factorisation's selects gone); one
-        // of 4,096 with its synchronisation: 66 -> 61 us. With more instances it would take twice
-        // the wavefronts.
+        // without an instance: each group then takes a row of 16, where a broadcast is one
+        // instruction (and rides on the products for N = 8). Measured, groups of 8 lanes against
+        // rows of 16: 256 quartics of n = 8 36.8 / 31.6 us, of n = 5 35.5 / 30.5, HS45M of n = 8
+        // 71.2 / 63.5, branches 25.6 / 23.7; 4,096: 47.0 / 40.0, 41.8 / 36.3, 100 / 86, 34.0 / 31.1.
+        // With more instances it would take twice the wavefronts.
         if (s.share.per <= 4) {
             hipLaunchKernelGGL((group_kernel<Fam, N, 8, true>), dim3(grid), dim3(blk), 0, st, s);
             return;

@@ -77,3 +77,18 @@ def test_multiplier_loop(tron):
         few = solve(bt.subset(list(range(count))))
         agree(many[:-1], few[:-1], 8)
         assert np.array_equal(many[-1].reshape(-1, 40)[:count], few[-1].reshape(-1, 40))
+
+
+@pytest.mark.parametrize("family,n,group", [(W.QP4, 9, 8), (W.QP4, 16, 8), (W.QP4, 9, 16), (W.QP4, 16, 16), (W.HS45M, 16, 8), (W.HS45M, 16, 16)])
+def test_groups_to_16(tron, family, n, group):
+    bt = W.qp4_batch(2500, n, config_id=530 + n) if family == W.QP4 else W.hs45m_random_start(2500, n, config_id=530 + n)
+
+    def solve(b):
+        h = tron.Batch(family, n, batch=b.batch, spec=tron.plan_spec(group16=group))
+        r = result(h.solve(*tron.to_device(b)))
+        h.close()
+        return r
+
+    many = solve(bt)
+    for count in (1, 127, 129, 255, 257, 1025):
+        agree(many, solve(bt.subset(list(range(count)))), n)
