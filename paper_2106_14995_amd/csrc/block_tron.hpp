@@ -51,6 +51,7 @@ MT_INLINE glb_double *uni_p(glb_double *q) { return (glb_double *)uni64((uint64_
 template <int R_, int W_, bool kGlobal>
 struct BlockTron : TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec> {
     static constexpr int R = R_, W = W_, kRows = 64 * R;
+    static constexpr bool kTight = false;
     using Steps = TronSteps<BlockTron<R_, W_, kGlobal>, R_, LdsVec>;
     using Steps::n;
     using Steps::lane;

@@ -169,7 +169,7 @@ __global__ __launch_bounds__(64) void al_kernel(LaneArgs a, AlArgs al)
 // ------------------------------------------------------------------------------------
 // Solve instance b on one wavefront with its matrix array at M (scr: the LDS scratch of the
 // global-memory form, unused otherwise).
-template <class Fam, bool kGlobal>
+template <class Fam, bool kGlobal, bool kTight>
 __device__ __forceinline__ void wave_solve(const LaneArgs &a, int64_t b, double *M, double *scr)
 {
     const int n = a.nper ? a.nper[b] : a.n_uniform;
@@ -178,7 +178,7 @@ __device__ __forceinline__ void wave_solve(const LaneArgs &a, int64_t b, double 
     const int64_t t0 = a.ts ? (int64_t)wall_clock64() : 0;
     constexpr int R = Fam::R;
     const int lane = threadIdx.x & 63;
-    mt::WaveTron<Fam, kGlobal> s;
+    mt::WaveTron<Fam, kGlobal, kTight> s;
     s.n = n;
     s.ld = (n + 1) | 1;  // odd and > n: column n holds the factor's pivots
     s.lane = lane;
@@ -205,25 +205,31 @@ __device__ __forceinline__ void wave_solve(const LaneArgs &a, int64_t b, double 
     }
 }
 
-template <class Fam, bool kGlobal>
+template <class Fam, bool kGlobal, bool kTight>
 __device__ __forceinline__ void wave_body(const LaneArgs &a)
 {
     extern __shared__ double smem[];
     const int64_t t = blockIdx.x;
     if (t >= a.count) return;
     const int64_t b = a.index ? (int64_t)a.index[t] : t;
-    wave_solve<Fam, kGlobal>(a, b, kGlobal ? a.ws + t * a.ws_stride : smem, smem);
+    wave_solve<Fam, kGlobal, kTight>(a, b, kGlobal ? a.ws + t * a.ws_stride : smem, smem);
 }
 
-// Two builds of the same solver: one held to three waves per SIMD's worth of registers (it
-// spills a few), one that gets what it asks for (two waves per SIMD).
+// Two builds of the same solver: one held to three waves per SIMD's worth of registers (168; the
+// quartic's spills 4 of them), one that gets what it asks for (two waves per SIMD). The first
+// takes its addresses afresh in every step (kTight), and so does the second for two rows per lane
+// of a quartic. Against the builds that kept them throughout and spilled 52 (HS45M), 70 and, in the
+// persistent launch up to n = 64, 84 registers: 20,000 quartics of n = 9 478 -> 423 us, 12,000 of
+// n = 28 659 -> 568, 50,000 of n = 4..64 in the persistent launch 2,303 -> 2,043, 10,000 HS45M of
+// n = 24 53.7 -> 47.5, 1,024 quartics of n = 100 1,583 -> 1,511. Where registers are free the
+// addresses are better kept (2,048 of n = 64 599 -> 610 us without).
 template <class Fam>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void wave_kernel(LaneArgs a) { wave_body<Fam, false>(a); }
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void wave_kernel(LaneArgs a) { wave_body<Fam, false, true>(a); }
 
 template <class Fam>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void wave_kernel_big(LaneArgs a)
 {
-    wave_body<Fam, false>(a);
+    wave_body<Fam, false, std::is_same<Fam, mt::WaveFamQP4<2>>::value>(a);
 }
 
 // The plan's wave_global: the matrix array is the instance's slot of a global-memory workspace;
@@ -239,24 +245,17 @@ constexpr size_t global_lds_bytes()
 template <class Fam>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void wave_kernel_global(LaneArgs a)
 {
-    wave_body<Fam, true>(a);
+    wave_body<Fam, true, false>(a);
 }
 
 constexpr int kCus = 256;
 // Which of the two builds takes a batch of instances up to n = 64. The build for two waves per SIMD:
-//   from n = 44 on, where the LDS holds little more than that (12,000 of n = 44, three waves
-//     against two: 1,160 / 1,074 us; of n = 47 1,326 / 1,142; n = 40 still 1,000 / 1,009);
-//   where it needs no more rounds over the chip than the other, up to 2,048 instances and from
-//     3,073 to 4,096 (4,000 of n = 9 162 / 148 us, of n = 16 187 / 169; 3,000 of n = 16 139 / 149);
-//   for the quartics of n = 17 to 24 beyond that (12,000 of n = 17 554 / 520 us, of n = 24 636 / 620;
-//     n = 16 391 / 401, n = 28 680 / 675, n = 36 925 / 959).
-template <class Fam>
-static bool two_waves(int nmax, int64_t count)
-{
-    constexpr int64_t two = 2 * 4 * kCus, three = 3 * 4 * kCus;
-    if (nmax >= 44 || (count + two - 1) / two == (count + three - 1) / three) return true;
-    return std::is_same<Fam, mt::WaveFamQP4<1>>::value && nmax > 16 && nmax <= 24 && count > three;
-}
+//   up to 2,048 instances, which both take in one round over the chip (three waves against two:
+//     2,048 of n = 9 78 / 74 us, of n = 16 93 / 87, of n = 32 175 / 166; more of them: 2,500 of
+//     n = 16 114 / 124, 4,096 154 / 160, 12,000 330 / 380, 12,000 of n = 24 517 / 604);
+//   from n = 44 on, where the LDS holds little more than that (12,000 of n = 40 882 / 997 us, of
+//     n = 44 1,060 / 1,063, of n = 48 1,194 / 1,109; 4,096 of n = 42 438 / 429, of n = 44 455 / 429).
+static bool two_waves(int nmax, int64_t count) { return nmax >= 44 || count <= 2 * 4 * kCus; }
 constexpr size_t kCuLds = 160 * 1024;
 
 static size_t wave_lds_bytes(int nmax) { return sizeof(double) * (size_t)nmax * (size_t)((nmax + 1) | 1); }
@@ -271,7 +270,7 @@ static void launch_wave(const LaneArgs &a, int nmax, hipStream_t st)
     if constexpr (Fam::R > 1) {
         hipLaunchKernelGGL((wave_kernel_big<Fam>), dim3((unsigned)a.count), dim3(64), lds, st, a);
     } else {
-        if (two_waves<Fam>(nmax, a.count))
+        if (two_waves(nmax, a.count))
             hipLaunchKernelGGL((wave_kernel_big<Fam>), dim3((unsigned)a.count), dim3(64), lds, st, a);
         else
             hipLaunchKernelGGL((wave_kernel<Fam>), dim3((unsigned)a.count), dim3(64), lds, st, a);
@@ -429,8 +428,8 @@ __global__ __launch_bounds__(64 * kWaves) void pool_kernel(LaneArgs a, PoolArgs 
         const int need = (int)((mt_wave_matrix_doubles(n) * (int64_t)sizeof(double) + kPoolPage - 1) / kPoolPage);
         const int first = pool_alloc(ctl, p.pages, need, lane);
         double *M = smem + (size_t)first * (kPoolPage / sizeof(double));
-        if (Fam2::R > 1 && n > 64) wave_solve<Fam2, false>(a, b, M, nullptr);
-        else wave_solve<Fam1, false>(a, b, M, nullptr);
+        if (Fam2::R > 1 && n > 64) wave_solve<Fam2, false, kWaves == 12>(a, b, M, nullptr);
+        else wave_solve<Fam1, false, kWaves == 12>(a, b, M, nullptr);
         pool_free(ctl, first, need, lane);
     }
 }

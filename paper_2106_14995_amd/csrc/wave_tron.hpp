@@ -378,7 +378,8 @@ struct LdsVec {
 template <class Derived, int R_, class Vec = RegVec<R_>>
 struct TronSteps {
     static constexpr int R = R_;
-    int n, lane;
+    int n;
+    mutable int lane;          // (see renew)
     Vec hd;                    // H diagonal (own rows)
     Vec lo, hi, x, g;
     double xs[R];
@@ -393,6 +394,14 @@ struct TronSteps {
     MT_INLINE const Derived &self() const { return static_cast<const Derived &>(*this); }
     MT_INLINE int row(int r) const { return lane + 64 * r; }
     MT_INLINE bool valid(int r) const { return row(r) < n; }
+
+    // Called where a matrix step starts. With Derived::kTight the compiler takes the lane number for
+    // a new one, so that the addresses the step derives from it live in the step; it would else
+    // compute them all before the solve's first iteration, which costs registers throughout.
+    MT_INLINE void renew() const
+    {
+        if constexpr (Derived::kTight) asm volatile("" : "+v"(lane));
+    }
 
     template <class A, class B>
     MT_INLINE double dot(const A &a, const B &b) const
@@ -722,10 +731,12 @@ struct TronSteps {
 // (n <= 64 R).
 // kGlobal: the matrix array M lives in global memory (a device workspace, when the plan asks for
 // it) instead of LDS; only the scope of the ordering between the lanes' writes and reads changes.
-template <class Fam, bool kGlobal = false>
-struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
+// kTight: the build has fewer registers than the solve's addresses want (see renew).
+template <class Fam, bool kGlobal = false, bool kTight_ = false>
+struct WaveTron : TronSteps<WaveTron<Fam, kGlobal, kTight_>, Fam::R> {
     static constexpr int R = Fam::R;
-    using Steps = TronSteps<WaveTron<Fam, kGlobal>, Fam::R>;
+    static constexpr bool kTight = kTight_;
+    using Steps = TronSteps<WaveTron<Fam, kGlobal, kTight_>, Fam::R>;
     using Steps::n;
     using Steps::lane;
     using Steps::hd;
@@ -735,6 +746,7 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
     using Steps::lfm;
     using Steps::has_l;
     using Steps::row;
+    using Steps::renew;
     using Steps::valid;
     using Steps::dot;
     using Steps::comp;
@@ -858,6 +870,7 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
             hmul_global(v, y);
             return;
         }
+        renew();
         double acc[R][4];
         int kk[R];
         MT_UNROLL for (int r = 0; r < R; r++) kk[r] = row(r) < n ? row(r) : 0;
@@ -1070,6 +1083,7 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
     template <bool kBelow>
     MT_INLINE bool panel_factor(int j0)
     {
+        renew();
         const int il = lane & 15, cols = n - j0;
         const int ip = il < cols ? j0 + il : j0;
         const double *pr = M + (int)__umul24((unsigned)ip, (unsigned)ld);
@@ -1130,6 +1144,7 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
     // columns past n read row n - 1; their results are not kept.
     MT_INLINE bool chol_lds(const uint64_t (&fm)[R], double alpha)
     {
+        renew();
         typedef double d4 __attribute__((ext_vector_type(4)));
         const int lr = lane & 15, lq = lane >> 4;
 #pragma unroll 1
@@ -1362,6 +1377,7 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal>, Fam::R> {
     template <bool kUp>
     MT_INLINE void substitute(double (&b)[R]) const
     {
+        renew();
         const int il = lane & 15, nb = (n + 15) >> 4;
         double dl[16];
 #pragma unroll 1
