@@ -116,7 +116,7 @@ tron_err tron_batch_create(tron_batch **out, tron_family family, int64_t batch,
 /* Launch plan of a handle: instances with n <= lane_max_n are solved one per GPU lane (a
  * kernel per exact n); larger ones one per wavefront (of the quartic family, those of n > 128
  * and some of n > 64 one per workgroup), grouped into buckets by the first of
- * `edges` (increasing, <= 128) that holds them, with LDS sized for that edge. Buckets run
+ * `edges` (increasing, <= 128) that holds them, with LDS for the bucket's largest n. Buckets run
  * concurrently on `streams` streams; lane kernels use workgroups of lane_block (64 or 256).
  * pool_waves > 0 selects the persistent size-bucketed form instead (section 4.1, a single
  * kernel rather than one per size) for batches of mixed sizes up to n = 128: one launch

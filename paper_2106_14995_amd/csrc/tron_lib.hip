@@ -515,7 +515,8 @@ static void launch_lane_packs(tron_family fam, const LaneArgs &a, const int32_t 
 // batch handle
 // ------------------------------------------------------------------------------------
 struct Bucket {
-    int32_t nmax;      // largest n the bucket's kernel holds
+    int32_t nmax;      // the bucket's edge
+    int32_t top;       // its largest n, which wavefront buckets are launched for
     int32_t lanes;     // lanes per instance (1: lane kernel, 64: wave kernel)
     int64_t count;     // instances in the bucket
     int32_t *d_index;  // instance list (null when the bucket is the whole batch in order)
@@ -575,7 +576,7 @@ static void launch_bucket(tron_family fam, const Bucket &b, const LaneArgs &a0, 
     LaneArgs a = a0;
     a.ws = b.d_ws;
     a.ws_stride = b.ws_stride;
-    launch_wave_fam(fam, a, b.nmax, st);
+    launch_wave_fam(fam, a, b.top, st);
 }
 
 // The default plan: the autotuner's usual choice on large uneven batches. Edges every 8 up to
@@ -830,7 +831,7 @@ static tron_err build_plan(tron_batch *h, const std::vector<int32_t> &n, hipStre
             b.lane = m;
         } else {
             if (!has_wave_kernel(h->fam)) return mt_fail(TRON_ERR_UNSUPPORTED, "this family has no wave kernel");
-            b.nmax = h->n_uniform;
+            b.nmax = b.top = h->n_uniform;
             b.lanes = 64;
             b.lane = nullptr;
             if ((b.nmax > kLdsMaxN || (sp.wave_global && h->fam == TRON_FAMILY_QP4)) && !alloc_workspace(b))
@@ -863,6 +864,7 @@ static tron_err build_plan(tron_batch *h, const std::vector<int32_t> &n, hipStre
         h->buckets.push_back(Bucket{});
         Bucket &b = h->buckets.back();
         b.nmax = nmax;
+        b.top = n[list[0]];  // wavefront buckets are ordered largest first
         b.lanes = lanes;
         b.count = (int64_t)list.size();
         b.lane = fn;

@@ -91,3 +91,20 @@ def test_shift_retries(tron, n):
     h = tron.Batch(bt.family, n, batch=3)
     check_parity(bt, result(h.solve(*tron.to_device(bt))), oracle_ref(bt), convex=True)
     h.close()
+
+
+@pytest.mark.parametrize("nmax,count", [(24, 40), (64, 40), (128, 60), (128, 300)])
+def test_bucket_of_many_sizes(tron, nmax, count):
+    """One bucket for every size (edge 128): with n > 64 among them the small ones run on a
+    workgroup too, in a matrix array of their own stride; same bits as in the default plan."""
+    sizes = W.loguniform_sizes(count, 9, nmax, config_id=97)
+    sizes[:4] = [9, 16, 17, nmax]
+    bt = W.qp4_batch(count, sizes, config_id=97)
+    got = []
+    for spec in (None, tron.plan_spec(edges=[128], pool_waves=0)):
+        h = tron.Batch(bt.family, sizes, spec=spec)
+        got.append(result(h.solve(*tron.to_device(bt))))
+        h.close()
+    for k in got[0]:
+        assert np.array_equal(got[0][k], got[1][k]), k
+    check_parity(bt, got[1], oracle_ref(bt), convex=True)
