@@ -5,10 +5,10 @@
 namespace {
 
 template <int R, int W, bool kGlobal>
-__global__ __launch_bounds__(64 * W) void block_kernel(LaneArgs a)
+__global__ __launch_bounds__(64 * W) void block_kernel(LaneArgs a, int64_t first)
 {
     extern __shared__ double block_smem[];
-    const int64_t t = blockIdx.x;
+    const int64_t t = first + blockIdx.x;
     if (t >= a.count) return;
     const int64_t b = a.index ? (int64_t)a.index[t] : t;
     const int n = a.nper ? a.nper[b] : a.n_uniform;
@@ -49,11 +49,17 @@ __global__ __launch_bounds__(64 * W) void block_kernel(LaneArgs a)
     }
 }
 
+// a launch may not have 2^32 threads
+constexpr int64_t kMostGroups = 1 << 22;
+
 template <int R, int W, bool kGlobal>
 void launch(const LaneArgs &a, int nmax, hipStream_t st)
 {
     const size_t lds = mt::BlockTron<R, W, kGlobal>::lds_bytes(nmax);
-    hipLaunchKernelGGL((block_kernel<R, W, kGlobal>), dim3((unsigned)a.count), dim3(64 * W), lds, st, a);
+    for (int64_t first = 0; first < a.count; first += kMostGroups) {
+        const int64_t left = a.count - first, groups = left < kMostGroups ? left : kMostGroups;
+        hipLaunchKernelGGL((block_kernel<R, W, kGlobal>), dim3((unsigned)groups), dim3(64 * W), lds, st, a, first);
+    }
 }
 
 template <int R, int W, bool kGlobal>

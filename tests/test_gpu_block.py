@@ -108,3 +108,29 @@ def test_bucket_of_many_sizes(tron, nmax, count):
     for k in got[0]:
         assert np.array_equal(got[0][k], got[1][k]), k
     check_parity(bt, got[1], oracle_ref(bt), convex=True)
+
+
+def test_more_workgroups_than_one_launch_holds(tron):
+    """8,388,651 instances in one bucket on workgroups of 512 threads: more than 2^32 threads. All
+    but the first repeat 50 problems of n = 9, and so do their results."""
+    import torch
+    reps = (1 << 23) // 50 + 1
+    one, few = W.qp4_batch(1, 128, config_id=98), W.qp4_batch(50, 9, config_id=99)
+    d1, d = tron.to_device(one), tron.to_device(few)
+    sizes = np.full(1 + 50 * reps, 9, np.int32)
+    sizes[0] = 128
+    assert 512 * sizes.size >= 1 << 32
+    h = tron.Batch(W.QP4, sizes, spec=tron.plan_spec(edges=[128], pool_waves=0))
+    x, f, status, iters = h.solve(*[torch.cat([a, b.repeat(reps)]) for a, b in zip(d1, d)])
+    torch.cuda.synchronize()
+    h.close()
+    h = tron.Batch(W.QP4, 9, batch=50)
+    rx, rf, rs, ri = h.solve(*d)
+    torch.cuda.synchronize()
+    h.close()
+    assert bool((x[128:].view(reps, -1) == rx).all())
+    for a, b in ((f, rf), (status, rs), (iters, ri)):
+        assert bool((a[1:].view(reps, -1) == b).all())
+    h = tron.Batch(W.QP4, 128, batch=1)
+    assert bool((h.solve(*d1)[0] == x[:128]).all())
+    h.close()
