@@ -134,3 +134,41 @@ def test_more_workgroups_than_one_launch_holds(tron):
     h = tron.Batch(W.QP4, 128, batch=1)
     assert bool((h.solve(*d1)[0] == x[:128]).all())
     h.close()
+
+
+@pytest.mark.parametrize("n", [80, 128, 129, 200, 300])
+def test_starts_and_bounds(tron, n):
+    """Crossed bounds, a NaN start, no bounds and one-sided bounds among ordinary instances."""
+    bt = W.qp4_batch(6, n, config_id=310 + n)
+    at = lambda b, i: b * n + i
+    bt.lo[at(1, n - 1)] = 5.0                                      # l > u, in the last row
+    bt.x0[at(2, 70)] = np.nan
+    bt.lo[at(3, 0):at(4, 0)], bt.hi[at(3, 0):at(4, 0)] = -np.inf, np.inf
+    bt.lo[at(4, 0):at(5, 0):2], bt.hi[at(4, 1):at(5, 0):2] = -np.inf, np.inf
+    h = tron.Batch(bt.family, n, batch=6)
+    g = result(h.solve(*tron.to_device(bt)))
+    h.close()
+    ref = oracle_ref(bt)
+    assert list(g["status"]) == list(ref["status"]) == [0, 4, 3, 0, 0, 0]
+    assert np.array_equal(g["x"][at(1, 0):at(2, 0)], bt.x0[at(1, 0):at(2, 0)])
+    check_parity(bt, g, ref, convex=True)
+
+
+@pytest.mark.parametrize("n", [80, 128, 129, 200, 300])
+def test_in_place_and_warm(tron, n):
+    """x0 and x in one buffer; a start from a given radius and step length, which is the cold
+    start with that radius; a restart from the solution, which takes no iteration."""
+    import torch
+    bt = batch(3, n)
+    h = tron.Batch(bt.family, n, batch=3, opts=tron.options(delta0=0.5))
+    cold = result(h.solve(*tron.to_device(bt)))
+    params, lo, hi, x = tron.to_device(bt)
+    inplace = result(h.solve(params, lo, hi, x, x=x))
+    h.set_options(tron.options(warm=True))
+    h.set_state(torch.tensor([0.5] * 3 + [1.0] * 3, device="cuda", dtype=torch.float64))
+    warm = result(h.solve(*tron.to_device(bt)))
+    again = result(h.solve(params, lo, hi, x, x=x))
+    h.close()
+    for k in cold:
+        assert np.array_equal(cold[k], inplace[k]) and np.array_equal(cold[k], warm[k]), k
+    assert np.all(again["iters"] == 0) and np.array_equal(again["x"], cold["x"])
