@@ -142,13 +142,6 @@ MT_INLINE void fnma_row4x(double &d, double q, double m0, double m1, double m2, 
         : "+&v"(d)
         : "v"(q), "v"(m0), "v"(m1), "v"(m2), "v"(m3), "n"(S), "n"(S + D), "n"(S + 2 * D), "n"(S + 3 * D));
 }
-template <int S>
-MT_INLINE void fma_row(double &d, double q, double m)
-{
-    asm volatile("s_nop 1\n\t"
-        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
-        : "+&v"(d) : "v"(q), "v"(m), "n"(S));
-}
 // d -= (q0 in lane S) m0, then (q1 in lane S) m1: a column pair of a triangular solve, its even
 // column into e and its odd one into o
 template <int S>
@@ -410,7 +403,6 @@ struct TronSteps {
     double xs[R];
     double hc[R];              // H (xs - x) while hc_ok: the accepted Cauchy trial's product
     bool hc_ok;
-    uint64_t lfm[R];           // free set of the last factored pass
     bool has_l;
     double f, delta, alphac;
     int32_t iters;
@@ -627,7 +619,6 @@ struct TronSteps {
             MT_UNROLL for (int r = 0; r < R; r++) rv[r] = hc[r] + g[r];
             const double shift = self().precond(fm);
             has_l = true;
-            MT_UNROLL for (int r = 0; r < R; r++) lfm[r] = fm[r];
             double w[R];
             const int ex = pcg(fm, m, rv, w, cg_rtol, shift == 0.0);
             self().bwd(w);
@@ -768,7 +759,6 @@ struct WaveTron : TronSteps<WaveTron<Fam, kGlobal, kTight_>, Fam::R> {
     using Steps::lo;
     using Steps::hi;
     using Steps::x;
-    using Steps::lfm;
     using Steps::has_l;
     using Steps::row;
     using Steps::renew;
