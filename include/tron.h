@@ -224,7 +224,9 @@ tron_err tron_batch_set_state(tron_batch *h, const double *d_state, void *stream
 tron_err tron_batch_set_options(tron_batch *h, const tron_options *opt);
 
 /* Describe the launch plan: number of buckets, and for each bucket (up to max_buckets)
- * its largest n, its lanes per instance and its instance count, as 3 int32 per bucket. */
+ * its largest n (or the edge that holds it), its lanes per instance and its instance count, as
+ * 3 int32 per bucket. 64 lanes stand for the wavefront kernels and, of the quartic family above
+ * n = 64, for the workgroup kernel (512 lanes), which take a bucket by its size and count. */
 tron_err tron_batch_plan(const tron_batch *h, int32_t *nbuckets, int32_t *desc,
                          int32_t max_buckets);
 

@@ -11,9 +11,10 @@
 //
 // What bounds it: up to n = 256 the trips to L2 and the serial steps (pivots of a panel's
 // diagonal block, the substitutions' 16-row blocks) at one workgroup per CU, since 256
-// registers per lane leave two waves per SIMD; at n = 512 the traffic past L2 (47 GB in 13.4 ms
-// for 256 instances, 3.5 TB/s; matrix cores busy 15 %). Against one wave per instance: 512 x n =
-// 200 16.1 -> 3.7 ms, 512 x n = 512 157 -> 23.7 ms.
+// registers per lane leave two waves per SIMD; at n = 512 the traffic past L2 (49 GB in 13.7 ms
+// for 256 instances, 3.6 TB/s; matrix cores busy 15 %). Scratch is part of it: every wave keeps
+// vectors of the solve there across the matrix steps (1.7 KB per lane for n > 256, 0.5 KB up to
+// 256). Against one wave per instance: 512 x n = 200 16.4 -> 3.7 ms, 512 x n = 512 157 -> 24.0 ms.
 //
 // Where the matrices live:
 //   kGlobal false  H (upper triangle with diagonal) and L (strict lower triangle) share one
@@ -32,7 +33,7 @@ namespace mt {
 
 // The matrix steps are functions of their own: inlined at every use they overflow the
 // instruction cache and the register file. Arguments go by value, in registers, and pointers
-// carry their address space, so that nothing passes through scratch or generic addresses.
+// carry their address space, so that no argument passes through scratch or a generic address.
 #define MT_STEP __device__ __attribute__((noinline))
 
 typedef __attribute__((address_space(1))) double glb_double;

@@ -7,12 +7,12 @@
 #include "lane_tron.hpp"
 #include "tron.h"
 
-// Arguments of the lane-per-instance solve kernels.
 // instances per wavefront, and ceil(2^16 / per)
 struct WaveShare {
     int32_t per, inv;
 };
 
+// Arguments of the solve kernels.
 struct LaneArgs {
     const double *params, *lo, *hi, *x0;
     double *x, *f;

@@ -18,8 +18,8 @@
 // Cholesky factorisation is blocked in panels of 16 columns: FP64 matrix-core products form each
 // panel from the columns before it, and the panel is factored in registers (chol_lds); the
 // substitutions run in blocks of 16 rows. Per batch, against the form that broadcast by readlane
-// and solved row by row: 2,048 x n = 64 0.86 -> 0.60 ms, 4,096 x n = 48 0.67 -> 0.47 ms, 10,000 x
-// n = 24 0.55 -> 0.52 ms, 1,024 x n = 100 2.29 -> 1.59 ms, bitwise the same results.
+// and solved row by row: 2,048 x n = 64 0.85 -> 0.59 ms, 4,096 x n = 48 0.64 -> 0.45 ms, 10,000 x
+// n = 24 0.55 -> 0.45 ms, 1,024 x n = 100 2.32 -> 1.56 ms, bitwise the same results.
 //
 // The steps and readings are those of lane_tron.hpp (Algorithm 1 with the TRON ratio test,
 // the step measured in the trust region's norm, and the trapezoid reduction near rounding
