@@ -273,7 +273,7 @@ typedef struct tron_server tron_server;
 typedef struct {
     size_t hbm_budget;            /* device bytes for requests in flight and open sessions;
                                      also the size of the pinned host staging area          */
-    size_t lds_budget;            /* LDS bytes of wavefront-kernel instances in flight      */
+    size_t lds_budget;            /* LDS bytes of the instances with n > 8 in flight        */
     int32_t max_inflight;         /* launch groups on the device at once (>= 1)             */
     int32_t streams;              /* device streams the groups are dealt to (>= 1)          */
     int32_t coalesce;             /* 1: a launch group may take several queued requests     */
